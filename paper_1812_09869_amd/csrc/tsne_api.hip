@@ -41,8 +41,9 @@ Layout make_layout(int64_t n, int32_t d, int32_t mode, bool stats_only, bool imp
   L.a = take(np * 4);
   L.r = take(np * 4);
   L.evals = take(np * 4);
-  L.part = take(sz * (size_t)L.nb * L.nb * T * 16);
-  L.zpart = take(sz * (size_t)L.nt * 8);
+  L.split = L.nb <= kSplitNb ? kUnits : 1;
+  L.part = take(sz * (size_t)L.nb * L.nb * L.split * T * 16);
+  L.zpart = take(sz * (size_t)L.nt * 4 * kUnits);
   L.cpart = take(sz * (size_t)L.nt * 16);
   L.ppart = take(sz * (size_t)L.nt * 16);
   L.meanpart = take(sz * (size_t)L.nb * kMeanPartsPerBlock * 16);
@@ -363,10 +364,9 @@ size_t tsne_batch_workspace_bytes(int32_t count) {
 }
 
 static int batch_totals(const char *fn, const tsne_batch_problem *pr, int32_t count,
-                        int64_t &tiles, int64_t &blocks) {
+                        tsne::BatchTotals &tot) {
   if (!pr || count < 1) return fail(TSNE_E_ARG, "%s: no problems", fn);
-  tiles = 0;
-  blocks = 0;
+  tot = tsne::BatchTotals{};
   for (int32_t p = 0; p < count; ++p) {
     if (!pr[p].ws || !pr[p].y || !pr[p].u || !pr[p].g)
       return fail(TSNE_E_ARG, "%s: null pointer in problem %d", fn, p);
@@ -374,18 +374,23 @@ static int batch_totals(const char *fn, const tsne_batch_problem *pr, int32_t co
     if (!aligned(pr[p].ws, 256))
       return fail(TSNE_E_WORKSPACE, "%s: problem %d: ws not 256-byte aligned", fn, p);
     const tsne::Layout L = tsne::make_layout(pr[p].n, 1, TSNE_DIST_FP64);
-    tiles += L.nt;
-    blocks += L.nb;
+    tot.tiles += L.nt;
+    tot.blocks += L.nb;
+    if (L.split > 1)
+      tot.units += L.nt * L.split;
+    else
+      tot.whole += L.nt;
   }
-  if (tiles >= ((int64_t)1 << 31) || blocks >= ((int64_t)1 << 31))
+  if (tot.tiles >= ((int64_t)1 << 31) || tot.blocks >= ((int64_t)1 << 31) ||
+      tot.units >= ((int64_t)1 << 31))
     return fail(TSNE_E_ARG, "%s: batch too large for one launch", fn);
   return TSNE_OK;
 }
 
 int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *batch_ws,
                     size_t batch_ws_bytes, void *stream) {
-  int64_t tiles, blocks;
-  if (int rc = batch_totals("tsne_batch_plan", problems, count, tiles, blocks)) return rc;
+  tsne::BatchTotals tot;
+  if (int rc = batch_totals("tsne_batch_plan", problems, count, tot)) return rc;
   if (!batch_ws || !aligned(batch_ws, 256))
     return fail(TSNE_E_WORKSPACE, "tsne_batch_plan: batch_ws null or misaligned");
   const size_t need = tsne_batch_workspace_bytes(count);
@@ -397,10 +402,11 @@ int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *bat
   tsne::BatchHdr *bh = reinterpret_cast<tsne::BatchHdr *>(host);
   bh->magic = tsne::kBatchMagic;
   bh->count = count;
-  bh->total_tiles = tiles;
-  bh->total_blocks = blocks;
+  bh->total_tiles = tot.tiles;
+  bh->total_blocks = tot.blocks;
+  bh->total_units = tot.units;
   tsne::BatchEntry *tab = reinterpret_cast<tsne::BatchEntry *>(host + tsne::kBatchHdrBytes);
-  int64_t t0 = 0;
+  int64_t t0 = 0, u0 = 0;
   int32_t b0 = 0;
   for (int32_t p = 0; p < count; ++p) {
     const tsne::Layout L = tsne::make_layout(problems[p].n, 1, TSNE_DIST_FP64);
@@ -429,6 +435,9 @@ int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *bat
     e.nb = L.nb;
     e.tile0 = t0;
     e.blk0 = b0;
+    e.split = L.split;
+    e.unit0 = u0;
+    if (L.split > 1) u0 += L.nt * L.split;
     t0 += L.nt;
     b0 += L.nb;
   }
@@ -441,11 +450,11 @@ int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *bat
 
 int tsne_batch_step(const tsne_batch_problem *problems, int32_t count, const void *batch_ws,
                     const tsne_step_params *prm, void *stream) {
-  int64_t tiles, blocks;
-  if (int rc = batch_totals("tsne_batch_step", problems, count, tiles, blocks)) return rc;
+  tsne::BatchTotals tot;
+  if (int rc = batch_totals("tsne_batch_step", problems, count, tot)) return rc;
   if (!batch_ws || !prm) return fail(TSNE_E_ARG, "tsne_batch_step: null pointer");
   if (int rc = check_params("tsne_batch_step", prm)) return rc;
-  return hip_check(tsne::launch_batch_step(batch_ws, count, tiles, blocks, prm->exaggeration,
+  return hip_check(tsne::launch_batch_step(batch_ws, count, tot, prm->exaggeration,
                                            prm->momentum, prm->learning_rate, prm->min_gain,
                                            prm->recentre, prm->lr_rule, (hipStream_t)stream),
                    "tsne_batch_step");
@@ -453,11 +462,10 @@ int tsne_batch_step(const tsne_batch_problem *problems, int32_t count, const voi
 
 int tsne_batch_cost(const tsne_batch_problem *problems, int32_t count, const void *batch_ws,
                     double *out, void *stream) {
-  int64_t tiles, blocks;
-  if (int rc = batch_totals("tsne_batch_cost", problems, count, tiles, blocks)) return rc;
+  tsne::BatchTotals tot;
+  if (int rc = batch_totals("tsne_batch_cost", problems, count, tot)) return rc;
   if (!batch_ws || !out) return fail(TSNE_E_ARG, "tsne_batch_cost: null pointer");
-  return hip_check(tsne::launch_batch_cost(batch_ws, count, tiles, blocks, out,
-                                           (hipStream_t)stream),
+  return hip_check(tsne::launch_batch_cost(batch_ws, count, tot, out, (hipStream_t)stream),
                    "tsne_batch_cost");
 }
 

@@ -22,12 +22,21 @@ namespace tsne {
 // tile holds the pairs (row tr + 16 (s / 4), column tc + 16 (4 (s % 4) + e)),
 // e = 0..3, so every wave-wide float4 load is one contiguous 1 KiB segment.
 // ---------------------------------------------------------------------------
-constexpr int kMeanPartsPerBlock = 2;  // re-centring partial sums per row block
+constexpr int kMeanPartsPerBlock = 4;  // re-centring partial sums per row block (at most)
 constexpr int64_t kImplicitTiles = 2048;  // implicit P: tiles recomputed per force launch (at least)
 constexpr int T = 256;             // tile edge
 constexpr int TT4 = T * T / 4;     // float4 per tile
 constexpr int kThreads = 256;      // threads per tile workgroup
 constexpr int kCalGroup = 4;       // row blocks per launch of the per-row search
+// Problems of at most kSplitNb row blocks (2,048 points) run the force pass in
+// units of a quarter tile (kUnits = 4 per tile, 64 rows x 256 columns each): a
+// whole tile is 256 pairs per thread, and a small problem has too few tiles to
+// fill the chip. The rule looks at n alone, so that a problem's sums are the
+// same in a single, a batched and an implicit-P pass (k_force_unit says why the
+// line lies there).
+constexpr int kSplitNb = 8;
+constexpr int kUnits = 4;
+constexpr int kUnitRows = T / kUnits;
 constexpr uint64_t kMagic = 0x74534E4533353501ull;
 
 // Error bits of the device flag word.
@@ -56,6 +65,7 @@ static_assert(sizeof(Hdr) <= 256, "header must fit its slot");
 struct Layout {
   int64_t n = 0, npad = 0, nt = 0;
   int32_t nb = 0, d = 0, dpad = 0, mode = 0;
+  int32_t split = 1;  // units per tile of the force pass (kUnits or 1)
   // byte offsets from the workspace base
   size_t hdr = 0, beta = 0, S = 0, H = 0, m = 0, a = 0, r = 0, evals = 0;
   size_t P = 0, part = 0, zpart = 0, cpart = 0, ppart = 0, meanpart = 0;
@@ -120,6 +130,8 @@ struct BatchEntry {
   Hdr *h;
   int64_t n, nt, tile0;  // tile0: first global tile index of this problem
   int32_t nb, blk0;      // blk0: first global row-block index of this problem
+  int64_t unit0;         // first global unit (problems with split = kUnits; the others have none)
+  int32_t split, pad;
 };
 
 // Header of a batch workspace, followed by `count` BatchEntry records.
@@ -151,7 +163,12 @@ struct BatchHdr {
   uint64_t magic;
   int32_t count;
   int32_t pad;
-  int64_t total_tiles, total_blocks;
+  int64_t total_tiles, total_blocks, total_units;
+};
+// Totals of a batch, computed on the host from the problems' sizes. units:
+// quarter tiles of the problems that are split; whole: tiles of the others.
+struct BatchTotals {
+  int64_t tiles = 0, blocks = 0, units = 0, whole = 0;
 };
 constexpr size_t kBatchHdrBytes = 256;
 
@@ -213,11 +230,11 @@ hipError_t launch_gradient_only(const Layout &L, void *ws, float alpha, float *g
                                 double *z_out, hipStream_t stream);
 hipError_t launch_cost(const Layout &L, void *ws, const float *y, double *out,
                        hipStream_t stream);
-hipError_t launch_batch_cost(const void *batch_ws, int count, int64_t total_tiles,
-                             int64_t total_blocks, double *out, hipStream_t stream);
-hipError_t launch_batch_step(const void *batch_ws, int count, int64_t total_tiles,
-                             int64_t total_blocks, float alpha, float mu, float eta,
-                             float min_gain, int recentre, int lr_rule, hipStream_t stream);
+hipError_t launch_batch_cost(const void *batch_ws, int count, const BatchTotals &tot, double *out,
+                             hipStream_t stream);
+hipError_t launch_batch_step(const void *batch_ws, int count, const BatchTotals &tot, float alpha,
+                             float mu, float eta, float min_gain, int recentre, int lr_rule,
+                             hipStream_t stream);
 hipError_t launch_export_p_rows(const Layout &L, void *ws, int64_t row0, int64_t nrows,
                                 float *out, hipStream_t stream);
 hipError_t launch_export_scalars(const Layout &L, void *ws, double *out, hipStream_t stream);

@@ -29,14 +29,14 @@ namespace {
 constexpr double kLn2 = 0.69314718055994530942;
 
 __device__ inline float2 *part_rep(float4 *part) { return reinterpret_cast<float2 *>(part); }
-__device__ inline float2 *part_att(float4 *part, int32_t nb) {
-  return reinterpret_cast<float2 *>(part) + (size_t)nb * nb * T;
+__device__ inline float2 *part_att(float4 *part, int32_t nb, int split = 1) {
+  return reinterpret_cast<float2 *>(part) + (size_t)nb * nb * split * T;
 }
 __device__ inline const float2 *part_rep(const float4 *part) {
   return reinterpret_cast<const float2 *>(part);
 }
-__device__ inline const float2 *part_att(const float4 *part, int32_t nb) {
-  return reinterpret_cast<const float2 *>(part) + (size_t)nb * nb * T;
+__device__ inline const float2 *part_att(const float4 *part, int32_t nb, int split = 1) {
+  return reinterpret_cast<const float2 *>(part) + (size_t)nb * nb * split * T;
 }
 
 __device__ inline void flag_error(Hdr *h, uint32_t bit) { atomicOr(&h->err, bit); }
@@ -558,6 +558,44 @@ __global__ __launch_bounds__(256, 2) void k_force_full(const float4 *__restrict_
   }
 }
 
+// Both kinds of tile in one launch on the caller's stream, a tile to a
+// workgroup, for problems of at most kAnyTiles tiles (75 row blocks). There
+// the pass is a few tiles deep (one tile with P alone takes 18 us), and the
+// fork to a second stream, the join and the two kernels' separate ends cost
+// more than the all-zero kernel's four workgroups per CU bring. An iteration
+// (one launch against two streams): n = 4,500 31 us against 55, 12,345 59
+// against 69, 16,000 77 against 85, 20,000 104 against 108, 25,000 146 against
+// 140, 65,536 807 against 708.
+constexpr int64_t kAnyTiles = 2850;
+// For a batch, by all its tiles: 501 tiles 46 us a sweep against 70, 1,341 78
+// against 102, 2,146 95 against 114, 5,796 225 against 227, 21,753 676 against
+// 611.
+constexpr int64_t kAnyTilesBatched = 4096;
+__global__ __launch_bounds__(256, 2) void k_force_any(const float4 *__restrict__ P,
+                                                      const float2 *__restrict__ Y, int64_t n,
+                                                      int32_t nb, float4 *__restrict__ part,
+                                                      float *__restrict__ zpart,
+                                                      const int2 *__restrict__ tmap,
+                                                      const uint8_t *__restrict__ nz, Hdr *h) {
+  __shared__ union {
+    ForceSmem full;
+    ZeroSmem zero;
+  } sm;
+  if (!ready_is(h, n, 1)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) flag_error(h, kErrState);
+    return;
+  }
+  const int64_t tile = blockIdx.x;
+  float2 yc[16];
+  if (nz[tile]) {
+    const TileCtx c = tile_begin(Y, n, nb, tmap, tile, yc, sm.full);
+    full_tile_body(c, yc, P, part, nb, zpart, tile, tile, sm.full);
+  } else {
+    const TileCtx c = tile_begin(Y, n, nb, tmap, tile, yc, sm.zero);
+    zero_tile_body(c, yc, part, zpart, tile, sm.zero);
+  }
+}
+
 // Implicit P: the nonzero tiles among tile0 .. tile0 + gridDim.x - 1 (whole
 // block rows), whose P was just recomputed into the buffer Pb (tile
 // tile0 + x at slot x); the all-zero ones are k_force_zero's.
@@ -581,6 +619,283 @@ __global__ __launch_bounds__(256, 2) void k_force_range(const float4 *__restrict
 }
 
 // ----------------------------------------------------------------------------
+// Small problems (at most kSplitNb row blocks): the force pass in quarter
+// tiles. Unit p of tile (I, J) covers the tile's rows 64 p .. 64 p + 63 (k = 4 p
+// .. 4 p + 3 of every thread) against all 256 columns, with the thread layout
+// of a whole tile. What bounds a small problem is the length of one
+// workgroup's work (256 pairs per thread of a whole tile, 18 us) on a chip
+// that is mostly idle, the launches, and the waits between two streams. So:
+//   - four workgroups per tile, one launch on the caller's stream for tiles
+//     with and without P (no fork and join);
+//   - the unit reads the map through the order itself (no gather launch), and
+//     the diagonal tiles' first unit writes the block's extent of the map;
+//   - its rows of P go straight to registers, two rows ahead (with four rows
+//     in all, a ring through LDS has nothing left to hide; one row ahead in
+//     the batch kernel that also holds the whole-tile body, which spills with
+//     two);
+//   - column sums: the four row groups of a wave meet by lane swaps, each
+//     swap halving the registers that carry on (96 instructions for 64
+//     values), so LDS holds one float4 per wave and column instead of
+//     sixteen: 16 KB instead of 66.
+// Slots: the row side of unit (I, J, p) is rows 64 p .. of slot (I, J, 0); its
+// column side is slot (J, I, p), so a column slot is four partial sums that
+// the update adds in FP64.
+// At n = 2,000 the pass takes 10.8 us (whole tiles: 18.4 us, a gather launch
+// of 3.4 us and an idle all-zero launch on the second stream), an iteration
+// 18.7 us against 54 on two streams (n = 300: 15.8 against 54). The rule ends
+// at eight row blocks because a unit's column sums cost a batch, which has
+// tiles enough, 12% of an all-zero tile's work (n = 4,000: 28 us in units, 30
+// in whole tiles and one launch).
+// ----------------------------------------------------------------------------
+struct UnitSmem {
+  float4 col[2][4][T];  // two buffers, by parity of the unit
+  float2 yrow[T];
+  float zred[kUnits][4];
+};
+
+// lanes l and l ^ 32 (l ^ 16) exchange halves: lanes of the lower half (even
+// rows of 16) return a summed over the pair, the others b
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+// Sum of one component over the wave's four row groups: c[m] holds the
+// thread's column tc + 16 m; on return lane group g = lane / 16 holds columns
+// tc + 16 (m + 4 (g & 1) + 8 (g >> 1)) in o[m], m = 0 .. 3.
+__device__ __forceinline__ void col_fold(const float (&c)[16], float (&o)[4]) {
+  float h[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) h[m] = swap_add32(c[m], c[m + 8]);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) o[m] = swap_add16(h[m], h[m + 4]);
+}
+
+// Units p0 .. p1 - 1 of one tile; the rows of P run through the units' joints
+// without a break, AHEAD rows ahead in registers. prep and patt: the partial
+// sums of the problem.
+template <bool FULL, bool DIAG, bool EDGE, int AHEAD>
+__device__ __forceinline__ void unit_rows(const float4 *__restrict__ tp, const float2 (&yc)[16],
+                                          uint32_t rvalid, uint32_t cvalid, int p0, int p1, int t,
+                                          int tr, int tc, float2 *__restrict__ prep,
+                                          float2 *__restrict__ patt, size_t rslot, size_t cslot,
+                                          UnitSmem &sm) {
+  constexpr int K = kUnitRows / 16;
+  float4 pv[AHEAD + 1][4];
+  if (FULL) {
+#pragma unroll
+    for (int kk = 0; kk < AHEAD; ++kk)
+#pragma unroll
+      for (int mq = 0; mq < 4; ++mq) pv[kk][mq] = tp[((K * p0 + kk) * 4 + mq) * 256 + t];
+  }
+#pragma unroll 1
+  for (int p = p0; p < p1; ++p) {
+    float4 mine = make_float4(0.f, 0.f, 0.f, 0.f);  // row sums: lane tc keeps row tr + 16 (tc & 3)
+    float cax[16], cay[16], crx[16], cry[16], z = 0.f;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) cax[m] = cay[m] = crx[m] = cry[m] = 0.f;
+#pragma unroll 1
+    for (int k = K * p; k < K * (p + 1); ++k) {
+      if (FULL) {
+        const int nk = k + AHEAD < K * p1 ? k + AHEAD : K * p1 - 1;  // past the end: unused
+#pragma unroll
+        for (int mq = 0; mq < 4; ++mq) pv[AHEAD][mq] = tp[(nk * 4 + mq) * 256 + t];
+      }
+      const float2 yi = sm.yrow[tr + 16 * k];
+      const uint32_t rowbit = (rvalid >> k) & 1u;
+      float ax = 0.f, ay = 0.f, rx = 0.f, ry = 0.f;
+#pragma unroll
+      for (int m = 0; m < 16; ++m) {
+        const float dx = yi.x - yc[m].x, dy = yi.y - yc[m].y;
+        const float q = fmaf(dx, dx, fmaf(dy, dy, 1.0f));
+        float w = __builtin_amdgcn_rcpf(q);
+        if (DIAG) {
+          if (tr == tc && k == m) w = 0.f;
+        }
+        if (EDGE) {
+          if (!(rowbit & (cvalid >> m) & 1u)) w = 0.f;
+        }
+        z += w;
+        const float w2 = w * w;
+        rx = fmaf(w2, dx, rx);
+        ry = fmaf(w2, dy, ry);
+        if (!DIAG) {
+          crx[m] = fmaf(-w2, dx, crx[m]);
+          cry[m] = fmaf(-w2, dy, cry[m]);
+        }
+        if (FULL) {
+          const float4 v = pv[0][m >> 2];
+          const float pp = (m & 3) == 0 ? v.x : (m & 3) == 1 ? v.y : (m & 3) == 2 ? v.z : v.w;
+          const float pw = pp * w;
+          ax = fmaf(pw, dx, ax);
+          ay = fmaf(pw, dy, ay);
+          if (!DIAG) {
+            cax[m] = fmaf(-pw, dx, cax[m]);
+            cay[m] = fmaf(-pw, dy, cay[m]);
+          }
+        }
+      }
+      float4 r = make_float4(0.f, 0.f, row16_sum(rx), row16_sum(ry));
+      if (FULL) {
+        r.x = row16_sum(ax);
+        r.y = row16_sum(ay);
+#pragma unroll
+        for (int mq = 0; mq < 4; ++mq)
+#pragma unroll
+          for (int a = 0; a < AHEAD; ++a) pv[a][mq] = pv[a + 1][mq];
+      }
+      if ((tc & 3) == k - K * p) mine = r;
+    }
+    static_assert(K == 4, "one row per two bits of tc");
+    if (tc < K) {
+      const size_t row = rslot + tr + 16 * (K * p + tc);
+      prep[row] = make_float2(mine.z, mine.w);
+      if (FULL) patt[row] = make_float2(mine.x, mine.y);
+    }
+    z = wave_sum_f(z);
+    if ((t & 63) == 0) sm.zred[p][t >> 6] = z;
+    if (!DIAG) {
+      float fx[4], fy[4], gx[4] = {}, gy[4] = {};
+      col_fold(crx, fx);
+      col_fold(cry, fy);
+      if (FULL) {
+        col_fold(cax, gx);
+        col_fold(cay, gy);
+      }
+      // two buffers: the barrier below stands between the reads of this unit
+      // and the writes of the next but one
+      float4(*col)[T] = sm.col[p & 1];
+      const int g = (t & 63) >> 4;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        col[t >> 6][tc + 16 * (m + 4 * (g & 1) + 8 * (g >> 1))] =
+            make_float4(gx[m], gy[m], fx[m], fy[m]);
+      __syncthreads();
+      float4 s = col[0][t];
+#pragma unroll
+      for (int q = 1; q < 4; ++q) {
+        const float4 v = col[q][t];
+        s.x += v.x;
+        s.y += v.y;
+        s.z += v.z;
+        s.w += v.w;
+      }
+      prep[cslot + (size_t)p * T] = make_float2(s.z, s.w);
+      if (FULL) patt[cslot + (size_t)p * T] = make_float2(s.x, s.y);
+    }
+  }
+}
+
+// Units p0 .. p1 - 1 of a tile. full: the tile holds nonzero P (at slot
+// pslot). KIND: 0 either, 1 only tiles with P, 2 only all-zero tiles. perm:
+// nullptr where Y is the gathered copy (zero past n; the gather wrote the
+// extents). The sums of a unit do not depend on how many share a workgroup.
+template <int KIND>
+__device__ __forceinline__ void unit_body(const float4 *__restrict__ P,
+                                          const float2 *__restrict__ Y,
+                                          const int32_t *__restrict__ perm, int64_t n, int32_t nb,
+                                          float4 *__restrict__ part, float *__restrict__ zpart,
+                                          float4 *__restrict__ extent, int2 ij, bool full,
+                                          int64_t tile, int64_t pslot, int p0, int p1,
+                                          UnitSmem &sm) {
+  const int I = ij.x, J = ij.y, t = threadIdx.x, l = t & 63, w = t >> 6;
+  const int tc = l & 15, tr = (l >> 4) + 4 * w;
+  const int64_t row0 = (int64_t)I * T, col0 = (int64_t)J * T;
+  // units wholly past the last point (of the last diagonal tile) add nothing
+  const int64_t left = n - row0;
+  const int pe = left >= (int64_t)kUnitRows * p1 ? p1 : (int)((left + kUnitRows - 1) / kUnitRows);
+  if (t >= pe && t < p1 && t >= p0) zpart[tile * kUnits + t] = 0.f;
+  if (pe <= p0) return;
+  float2 yc[16];
+  if (perm) {
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const int64_t c = col0 + tc + 16 * m;
+      yc[m] = c < n ? Y[perm[c]] : make_float2(0.f, 0.f);
+    }
+    if (t >= kUnitRows * p0 && t < kUnitRows * pe)
+      sm.yrow[t] = row0 + t < n ? Y[perm[row0 + t]] : make_float2(0.f, 0.f);
+  } else {
+#pragma unroll
+    for (int m = 0; m < 16; ++m) yc[m] = Y[col0 + tc + 16 * m];
+    sm.yrow[t] = Y[row0 + t];
+  }
+  const uint32_t rvalid = valid_bits(left, tr), cvalid = valid_bits(n - col0, tc);
+  __syncthreads();
+  if (perm && I == J && p0 == 0 && w == 0) {
+    // extent of the block's points (exact in any order)
+    float lox = INFINITY, hix = -INFINITY, loy = INFINITY, hiy = -INFINITY;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const bool ok = (cvalid >> m) & 1u;
+      lox = fminf(lox, ok ? yc[m].x : INFINITY);
+      hix = fmaxf(hix, ok ? yc[m].x : -INFINITY);
+      loy = fminf(loy, ok ? yc[m].y : INFINITY);
+      hiy = fmaxf(hiy, ok ? yc[m].y : -INFINITY);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+      lox = fminf(lox, __shfl_xor(lox, o));
+      hix = fmaxf(hix, __shfl_xor(hix, o));
+      loy = fminf(loy, __shfl_xor(loy, o));
+      hiy = fmaxf(hiy, __shfl_xor(hiy, o));
+    }
+    if (l == 0) extent[I] = make_float4(lox, hix, loy, hiy);
+  }
+  const float4 *tp = P + (size_t)pslot * TT4;
+  float2 *prep = part_rep(part), *patt = part_att(part, nb, kUnits);
+  const size_t rslot = ((size_t)I * nb + J) * kUnits * T;
+  const size_t cslot = ((size_t)J * nb + I) * kUnits * T + t;
+  const bool edge = col0 + T > n;
+#define TSNE_UNIT(D, E)                                                                          \
+  if (KIND != 2 && (KIND == 1 || full))                                                          \
+    unit_rows<true, D, E, KIND == 1 ? 1 : 2>(tp, yc, rvalid, cvalid, p0, pe, t, tr, tc, prep, patt, rslot, cslot,   \
+                          sm);                                                                   \
+  else                                                                                           \
+    unit_rows<false, D, E, 1>(tp, yc, rvalid, cvalid, p0, pe, t, tr, tc, prep, patt, rslot, cslot,  \
+                           sm)
+  if (I == J) {
+    TSNE_UNIT(true, true);
+  } else if (edge) {
+    TSNE_UNIT(false, true);
+  } else {
+    TSNE_UNIT(false, false);
+  }
+#undef TSNE_UNIT
+  __syncthreads();
+  if (t >= p0 && t < pe) {
+    const double zd = (double)sm.zred[t][0] + (double)sm.zred[t][1] + (double)sm.zred[t][2] +
+                      (double)sm.zred[t][3];
+    zpart[tile * kUnits + t] = (float)(zd * (I == J ? 1.0 : 2.0));
+  }
+}
+
+// key: -1 for a stored P, else the implicit key of a recomputed one (then the
+// buffer holds every tile).
+__global__ __launch_bounds__(256, 2) void k_force_unit(
+    const float4 *__restrict__ P, const float2 *__restrict__ Y, const int32_t *__restrict__ perm,
+    int64_t n, int32_t nb, float4 *__restrict__ part, float *__restrict__ zpart,
+    float4 *__restrict__ extent, const int2 *__restrict__ tmap, const uint8_t *__restrict__ nz,
+    int32_t key, Hdr *h) {
+  __shared__ UnitSmem sm;
+  if (!(key < 0 ? ready_is(h, n, 1)
+                : ready_is(h, n, 2) && implicit_key(h->d, h->mode) == key)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) flag_error(h, kErrState);
+    return;
+  }
+  const int64_t tile = blockIdx.x / kUnits;
+  const int p = (int)(blockIdx.x % kUnits);
+  unit_body<0>(P, Y, perm, n, nb, part, zpart, extent, tmap[tile], nz[tile] != 0, tile, tile, p,
+            p + 1, sm);
+}
+
+// ----------------------------------------------------------------------------
 // Reduce + update. kUpdPerBlock workgroups of kUpd threads per block of T
 // rows; thread (r, q) of a workgroup sums the slots s = q, q + kUpdSplit, ...
 // of its row r in order, and the kUpdSplit partial sums meet in LDS in q
@@ -591,7 +906,8 @@ __global__ __launch_bounds__(256, 2) void k_force_range(const float4 *__restrict
 constexpr int kUpd = 1024;
 constexpr int kUpdRows = 128;                 // rows per workgroup
 constexpr int kUpdPerBlock = T / kUpdRows;    // workgroups per row block
-static_assert(kUpdPerBlock == kMeanPartsPerBlock, "one re-centring partial per update workgroup");
+static_assert(kUpdPerBlock * kUpdRows / 64 == kMeanPartsPerBlock,
+              "at most one re-centring partial per wave of rows");
 constexpr int kUpdSplit = kUpd / kUpdRows;    // threads per row
 constexpr int kSlotLds = 4096;                // nonzero-slot list entries staged in LDS
 constexpr int kUpdBatch = 8;                  // repulsive-slot loads in flight per thread
@@ -752,11 +1068,38 @@ __device__ inline float2 gradient_of(double4 s, double alpha, double Z) {
   return make_float2((float)(4.0 * (alpha * s.x - s.z / Z)), (float)(4.0 * (alpha * s.y - s.w / Z)));
 }
 
-// Update (Eq. 10, descent): gains, momentum, position; per-workgroup sums of
-// the new positions for the re-centring. Workgroup wg of the problem covers
+// Update of row i (Eq. 10, descent) with gradient g: gains, momentum, position;
+// returns the new position. lr_rule 0: the given eta with adaptive gains;
+// lr_rule 1: eta of Eq. 11 and no gains (G is neither read nor written).
+__device__ __forceinline__ float2 update_row(int64_t i, float2 g, float2 *__restrict__ Y,
+                                             float2 *__restrict__ U, float2 *__restrict__ G,
+                                             float mu, float eta, float min_gain, int lr_rule,
+                                             float2 *__restrict__ grad_out) {
+  if (grad_out) grad_out[i] = g;
+  float2 u = U[i], y = Y[i];
+  if (lr_rule) {
+    u.x = mu * u.x - eta * g.x;
+    u.y = mu * u.y - eta * g.y;
+  } else {
+    float2 gn = G[i];
+    gn.x = ((g.x > 0.f) != (u.x > 0.f)) ? gn.x + 0.2f : gn.x * 0.8f;
+    gn.y = ((g.y > 0.f) != (u.y > 0.f)) ? gn.y + 0.2f : gn.y * 0.8f;
+    gn.x = fmaxf(gn.x, min_gain);
+    gn.y = fmaxf(gn.y, min_gain);
+    u.x = mu * u.x - eta * (gn.x * g.x);
+    u.y = mu * u.y - eta * (gn.y * g.y);
+    G[i] = gn;
+  }
+  y.x += u.x;
+  y.y += u.y;
+  U[i] = u;
+  Y[i] = y;
+  return y;
+}
+
+// The update of whole-tile problems, and per-workgroup sums of the new
+// positions for the re-centring. Workgroup wg of the problem covers
 // rows (wg % kUpdPerBlock) * kUpdRows ... of block wg / kUpdPerBlock.
-// lr_rule 0: the given eta with adaptive gains; lr_rule 1: eta of Eq. 11 and
-// no gains (G is neither read nor written).
 __device__ __forceinline__ void update_wg(const float4 *__restrict__ part,
                                           const int32_t *__restrict__ slots,
                                           const int32_t *__restrict__ nslots,
@@ -799,26 +1142,7 @@ __device__ __forceinline__ void update_wg(const float4 *__restrict__ part,
   double sx = 0.0, sy = 0.0;
   bool bad = false;
   if (q == 0 && ir < n) {
-    const int64_t i = perm[ir];
-    if (grad_out) grad_out[i] = g;
-    float2 u = U[i], y = Y[i];
-    if (lr_rule) {
-      u.x = mu * u.x - eta * g.x;
-      u.y = mu * u.y - eta * g.y;
-    } else {
-      float2 gn = G[i];
-      gn.x = ((g.x > 0.f) != (u.x > 0.f)) ? gn.x + 0.2f : gn.x * 0.8f;
-      gn.y = ((g.y > 0.f) != (u.y > 0.f)) ? gn.y + 0.2f : gn.y * 0.8f;
-      gn.x = fmaxf(gn.x, min_gain);
-      gn.y = fmaxf(gn.y, min_gain);
-      u.x = mu * u.x - eta * (gn.x * g.x);
-      u.y = mu * u.y - eta * (gn.y * g.y);
-      G[i] = gn;
-    }
-    y.x += u.x;
-    y.y += u.y;
-    U[i] = u;
-    Y[i] = y;
+    const float2 y = update_row(perm[ir], g, Y, U, G, mu, eta, min_gain, lr_rule, grad_out);
     sx = y.x;
     sy = y.y;
     bad = !(isfinite(g.x) && isfinite(g.y) && isfinite(y.x) && isfinite(y.y));
@@ -853,16 +1177,143 @@ __global__ __launch_bounds__(kUpd) void k_update(
             lr_rule, extent, grad_out, z_out, meanpart, h, blockIdx.x, sm);
 }
 
+// ----------------------------------------------------------------------------
+// Reduce + update of a problem that ran in units. What bounds it is the chain
+// of dependent memory latencies, not the few partial sums, so everything that
+// does not depend on another load is loaded at once: the partial sums of all
+// slots (those of all-zero tiles too, dropped by their tile's flag, instead of
+// a slot list that has to arrive first), the flags, the Z partials and the
+// order; one barrier then joins the row sums, Z and the rate of Eq. 11. At n =
+// 2,000: 6.5 us with 4.6 us of it at n = 300, against 6.8 and 6.3 us (and the
+// slot list's latency in every workgroup) for the whole-tile update.
+// Thread (r, q) sums the partial sums v = q, q + 8, ... of its row in order:
+// first the column slots (s < b, kUnits each), then the row slots (s >= b).
+// ----------------------------------------------------------------------------
+static_assert(kSplitNb * (kSplitNb + 1) / 2 * kUnits <= kUpd, "one Z partial per thread");
+
+// Row sums (valid for q == 0) and Z (every thread); ends with the barrier.
+__device__ __forceinline__ double4 unit_sums(const float4 *__restrict__ part,
+                                             const uint8_t *__restrict__ nz,
+                                             const float *__restrict__ zpart, int64_t nt,
+                                             int32_t nb, int b, int r, int q, double &Z,
+                                             UpdSmem &sm) {
+  const int t = threadIdx.x;
+  const int lower = kUnits * b, total = lower + (int)nb - b;
+  const float2 *pr = part_rep(part) + (size_t)b * nb * kUnits * T + r;
+  const float2 *pa = part_att(part, nb, kUnits) + (size_t)b * nb * kUnits * T + r;
+  const float zv = t < nt * kUnits ? zpart[t] : 0.f;
+  double ax = 0.0, ay = 0.0, rx = 0.0, ry = 0.0;
+  // four sums of each kind in flight (all of them up to eight row blocks)
+#pragma unroll 1
+  for (int v0 = q; v0 < total; v0 += 4 * kUpdSplit) {
+    float2 rv[4], av[4];
+    bool has[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int v = v0 + kUpdSplit * k;
+      rv[k] = av[k] = make_float2(0.f, 0.f);
+      has[k] = false;
+      if (v < total) {
+        const int u = v < lower ? v : lower + kUnits * (v - lower), s = u / kUnits;
+        rv[k] = pr[(size_t)u * T];
+        av[k] = pa[(size_t)u * T];  // not written for an all-zero tile: dropped below
+        has[k] = nz[s >= b ? tile_start(b, nb) + (s - b) : tile_start(s, nb) + (b - s)] != 0;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      rx += rv[k].x;
+      ry += rv[k].y;
+      ax += has[k] ? av[k].x : 0.f;
+      ay += has[k] ? av[k].y : 0.f;
+    }
+  }
+  const int rl = r % kUpdRows;
+  if (q > 0) sm.part[q - 1][rl] = make_double4(ax, ay, rx, ry);
+  const double zs = wave_sum_d((double)zv);
+  if ((t & 63) == 0) sm.red[0][t >> 6] = zs;
+  __syncthreads();
+  Z = 0.0;
+#pragma unroll
+  for (int w = 0; w < kUpd / 64; ++w) Z += sm.red[0][w];
+  if (q == 0) {
+#pragma unroll
+    for (int g = 0; g < kUpdSplit - 1; ++g) {
+      const double4 v = sm.part[g][rl];
+      ax += v.x;
+      ay += v.y;
+      rx += v.z;
+      ry += v.w;
+    }
+  }
+  return make_double4(ax, ay, rx, ry);
+}
+
+__device__ __forceinline__ void update_units_wg(
+    const float4 *__restrict__ part, const uint8_t *__restrict__ nz,
+    const float *__restrict__ zpart, int64_t nt, int64_t n, int32_t nb,
+    const int32_t *__restrict__ perm, float2 *__restrict__ Y, float2 *__restrict__ U,
+    float2 *__restrict__ G, float alpha, float mu, float eta, float min_gain, int lr_rule,
+    const float4 *__restrict__ extent, float2 *__restrict__ grad_out, double *__restrict__ z_out,
+    double2 *__restrict__ meanpart, Hdr *h, int wg, UpdSmem &sm) {
+  if (!state_ok(h, n)) return;
+  if (lr_rule) adaptive_eta(extent, nb, n, sm);  // published by the barrier below
+  const int b = wg / kUpdPerBlock, t = threadIdx.x, q = t / kUpdRows;
+  const int r = (wg % kUpdPerBlock) * kUpdRows + t % kUpdRows;
+  const int64_t ir = (int64_t)b * T + r;
+  const bool row = q == 0 && ir < n;
+  const int64_t i = row ? perm[ir] : 0;
+  double Z;
+  const double4 rs = unit_sums(part, nz, zpart, nt, nb, b, r, q, Z, sm);
+  if (lr_rule) eta = sm.eta;
+  if (wg == 0 && t == 0) {
+    h->z = Z;
+    if (z_out) *z_out = Z;
+    if (!isfinite(Z) || !(Z > 0.0)) flag_error(h, kErrNonFinite);
+  }
+  if (q > 0) return;  // whole waves: the rest belongs to the rows' two waves
+  double sx = 0.0, sy = 0.0;
+  if (row) {
+    const float2 g = gradient_of(rs, (double)alpha, Z);
+    const float2 y = update_row(i, g, Y, U, G, mu, eta, min_gain, lr_rule, grad_out);
+    sx = y.x;
+    sy = y.y;
+    if (!(isfinite(g.x) && isfinite(g.y) && isfinite(y.x) && isfinite(y.y)))
+      flag_error(h, kErrNonFinite);
+  }
+  sx = wave_sum_d(sx);
+  sy = wave_sum_d(sy);
+  // one partial sum of the mean per wave
+  if ((t & 63) == 0) meanpart[wg * (kUpdRows / 64) + (t >> 6)] = make_double2(sx, sy);
+}
+
+__global__ __launch_bounds__(kUpd) void k_update_units(
+    const float4 *__restrict__ part, const uint8_t *__restrict__ nz,
+    const float *__restrict__ zpart, int64_t nt, int64_t n, int32_t nb,
+    const int32_t *__restrict__ perm, float2 *__restrict__ Y, float2 *__restrict__ U,
+    float2 *__restrict__ G, float alpha, float mu, float eta, float min_gain, int lr_rule,
+    const float4 *__restrict__ extent, float2 *__restrict__ grad_out, double *__restrict__ z_out,
+    double2 *__restrict__ meanpart, Hdr *h) {
+  __shared__ UpdSmem sm;
+  update_units_wg(part, nz, zpart, nt, n, nb, perm, Y, U, G, alpha, mu, eta, min_gain, lr_rule,
+                  extent, grad_out, z_out, meanpart, h, blockIdx.x, sm);
+}
+
+// Partial sums of the mean: one per update workgroup, or per wave of rows.
+__host__ __device__ inline int32_t mean_parts(int32_t nb, int split) {
+  return nb * (split > 1 ? kMeanPartsPerBlock : kUpdPerBlock);
+}
+
 // Subtract the mean of the map from the rows of block `blk`.
 __device__ __forceinline__ void recentre_wg(const double2 *__restrict__ meanpart, int64_t n,
-                                            int32_t nb, float2 *__restrict__ Y, Hdr *h, int blk,
-                                            float2 &smean) {
+                                            int32_t nparts, float2 *__restrict__ Y, Hdr *h,
+                                            int blk, float2 &smean) {
   __shared__ double2 wred[4];
   if (!state_ok(h, n)) return;
   // strided partial sums over the 256 threads, the wave sums, then the four
   // wave results in order (a fixed order)
   double mx = 0.0, my = 0.0;
-  for (int b = threadIdx.x; b < nb * kUpdPerBlock; b += 256) {
+  for (int b = threadIdx.x; b < nparts; b += 256) {
     mx += meanpart[b].x;
     my += meanpart[b].y;
   }
@@ -886,9 +1337,10 @@ __device__ __forceinline__ void recentre_wg(const double2 *__restrict__ meanpart
 }
 
 __global__ __launch_bounds__(256) void k_recentre(const double2 *__restrict__ meanpart, int64_t n,
-                                                  int32_t nb, float2 *__restrict__ Y, Hdr *h) {
+                                                  int32_t nparts, float2 *__restrict__ Y,
+                                                  Hdr *h) {
   __shared__ float2 smean;
-  recentre_wg(meanpart, n, nb, Y, h, blockIdx.x, smean);
+  recentre_wg(meanpart, n, nparts, Y, h, blockIdx.x, smean);
 }
 
 // ----------------------------------------------------------------------------
@@ -923,6 +1375,51 @@ __device__ inline const BatchEntry *batch_table(const BatchHdr *bh) {
                                               kBatchHdrBytes);
 }
 
+// Last entry whose first unit is not after `key`. Every wave looks at 64
+// entries at a time (one load each), so the search is one or two memory
+// latencies instead of one per halving. Problems that are not split have no
+// units: they share their successor's first unit and are never the last; a
+// run of them at the end of the table starts past every unit.
+__device__ inline int find_unit_entry(const BatchEntry *tab, int count, int64_t key) {
+  int below = 0;
+  for (int b = 0; b < count; b += 64) {
+    const int p = b + (threadIdx.x & 63);
+    below += __popcll(__ballot(p < count && tab[p].unit0 <= key));
+  }
+  return below > 0 ? below - 1 : 0;
+}
+
+// Units of the split problems, `per` (1, 2 or 4) of one tile to a workgroup.
+__global__ __launch_bounds__(256, 2) void k_force_unit_batched(const BatchHdr *__restrict__ bh,
+                                                               int count, int64_t tiles,
+                                                               int64_t blocks, int64_t units,
+                                                               int per) {
+  __shared__ UnitSmem sm;
+  if (!batch_ok(bh, count, tiles, blocks) || bh->total_units != units) return;
+  const BatchEntry *tab = batch_table(bh);
+  const int64_t key = (int64_t)blockIdx.x * per;
+  const BatchEntry &e = tab[__builtin_amdgcn_readfirstlane(find_unit_entry(tab, count, key))];
+  const int64_t u = key - e.unit0;
+  if (e.split != kUnits || u < 0 || u >= e.nt * kUnits) return;
+  if (!ready_is(e.h, e.n, 1)) {
+    if (u == 0 && threadIdx.x == 0) flag_error(e.h, kErrState);
+    return;
+  }
+  const int64_t tile = u / kUnits;
+  const int p = (int)(u % kUnits);
+  unit_body<0>(e.P, e.Y, e.perm, e.n, e.nb, e.part, e.zpart, e.extent, e.tmap[tile],
+            e.nz[tile] != 0, tile, tile, p, p + per, sm);
+}
+
+// A batch of split and other problems: one launch per kind of tile for all of
+// them, a split problem's tile taken whole (its four units in turn), so that
+// neither kind of problem waits for the other's launch.
+template <class Smem>
+union BatchSmem {
+  Smem tile;
+  UnitSmem unit;
+};
+
 // All-zero tiles of the batch: launched over every tile of every problem
 // (the problem found by binary search on its first tile); a workgroup whose
 // position within its problem is past the count of all-zero tiles exits at
@@ -930,7 +1427,7 @@ __device__ inline const BatchEntry *batch_table(const BatchHdr *bh) {
 __global__ __launch_bounds__(256, 4) void k_force_zero_batched(const BatchHdr *__restrict__ bh,
                                                                int count, int64_t tiles,
                                                                int64_t blocks) {
-  __shared__ ZeroSmem sm;
+  __shared__ BatchSmem<ZeroSmem> sm;
   if (!batch_ok(bh, count, tiles, blocks)) return;
   const BatchEntry *tab = batch_table(bh);
   const int p = find_entry(tab, count, blockIdx.x, true);
@@ -943,9 +1440,51 @@ __global__ __launch_bounds__(256, 4) void k_force_zero_batched(const BatchHdr *_
   }
   if (i >= e.tcount[0]) return;
   const int64_t tile = e.tlist[i];
+  if (e.split > 1) {
+    unit_body<2>(nullptr, e.yp, nullptr, e.n, e.nb, e.part, e.zpart, nullptr, e.tmap[tile], false,
+                 tile, 0, 0, kUnits, sm.unit);
+    return;
+  }
   float2 yc[16];
-  const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm);
-  zero_tile_body(c, yc, e.part, e.zpart, tile, sm);
+  const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm.tile);
+  zero_tile_body(c, yc, e.part, e.zpart, tile, sm.tile);
+}
+
+// Every tile of the batch in one launch, a tile (of a split problem: its four
+// units in turn) to a workgroup, for batches of at most kAnyTilesBatched tiles
+// (k_force_any says why).
+__global__ __launch_bounds__(256, 2) void k_force_any_batched(const BatchHdr *__restrict__ bh,
+                                                              int count, int64_t tiles,
+                                                              int64_t blocks) {
+  __shared__ union {
+    ForceSmem full;
+    ZeroSmem zero;
+    UnitSmem unit;
+  } sm;
+  if (!batch_ok(bh, count, tiles, blocks)) return;
+  const BatchEntry *tab = batch_table(bh);
+  const int p = find_entry(tab, count, blockIdx.x, true);
+  const BatchEntry &e = tab[p];
+  const int64_t tile = (int64_t)blockIdx.x - e.tile0;
+  if (tile < 0 || tile >= e.nt) return;
+  if (!ready_is(e.h, e.n, 1)) {
+    if (tile == 0 && threadIdx.x == 0) flag_error(e.h, kErrState);
+    return;
+  }
+  const bool full = e.nz[tile] != 0;
+  if (e.split > 1) {
+    unit_body<0>(e.P, e.yp, nullptr, e.n, e.nb, e.part, e.zpart, nullptr, e.tmap[tile], full, tile,
+                 tile, 0, kUnits, sm.unit);
+    return;
+  }
+  float2 yc[16];
+  if (full) {
+    const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm.full);
+    full_tile_body(c, yc, e.P, e.part, e.nb, e.zpart, tile, tile, sm.full);
+  } else {
+    const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm.zero);
+    zero_tile_body(c, yc, e.part, e.zpart, tile, sm.zero);
+  }
 }
 
 // The nonzero tiles of every problem form one list (problem by problem, each
@@ -958,20 +1497,37 @@ __device__ inline void full_range(const BatchEntry &e, int64_t &first, int64_t &
   cnt = min(max((int64_t)e.tcount[1], (int64_t)0), e.nt - first);
 }
 
+// One tile with P. Ends with a workgroup barrier.
+__device__ __forceinline__ void full_tile_of(const BatchEntry &e, int64_t tile,
+                                             BatchSmem<ForceSmem> &sm) {
+  if (e.split > 1) {
+    unit_body<1>(e.P, e.yp, nullptr, e.n, e.nb, e.part, e.zpart, nullptr, e.tmap[tile], true, tile,
+                 tile, 0, kUnits, sm.unit);
+    __syncthreads();
+    return;
+  }
+  float2 yc[16];
+  const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm.tile);
+  full_tile_body(c, yc, e.P, e.part, e.nb, e.zpart, tile, tile, sm.tile);
+}
+
 // Problems whose list offsets a workgroup of the nonzero-tile kernel keeps in
 // LDS (larger batches walk the table serially).
 constexpr int kBatchLds = 1024;
 
+// WALK: a batch of more than kBatchLds problems (an instance of its own: with
+// both loops in one kernel the tile bodies spill).
+template <bool WALK>
 __global__ __launch_bounds__(256, 2) void k_force_full_batched(const BatchHdr *__restrict__ bh,
                                                                int count, int64_t tiles,
                                                                int64_t blocks) {
-  __shared__ ForceSmem sm;
-  __shared__ int64_t pre[kBatchLds + 1];  // list position of problem p's first nonzero tile
+  __shared__ BatchSmem<ForceSmem> sm;
+  __shared__ int64_t pre[WALK ? 1 : kBatchLds + 1];  // list position of a problem's first nonzero tile
   __shared__ int64_t nzero_s;
   if (!batch_ok(bh, count, tiles, blocks)) return;
   const BatchEntry *tab = batch_table(bh);
   const int t = threadIdx.x;
-  if (count <= kBatchLds) {
+  if constexpr (!WALK) {
     // one wave: lane l sums the nonzero and all-zero counts of problems
     // 16 l .. 16 l + 15 (loads in flight together), then an inclusive scan
     // over the lanes gives every problem's offset
@@ -1025,15 +1581,16 @@ __global__ __launch_bounds__(256, 2) void k_force_full_batched(const BatchHdr *_
         else
           hi = mid - 1;
       }
+      // the same in every lane, though it came through LDS: the entry's fields
+      // stay in scalar registers
+      lo = __builtin_amdgcn_readfirstlane(lo);
       const BatchEntry &e = tab[lo];
       int64_t first, cnt;
       full_range(e, first, cnt);
       const int64_t i = g - pre[lo];
       if (i >= cnt) continue;  // not reached: pre counts exactly cnt positions
       const int64_t tile = e.tlist[first + i];
-      float2 yc[16];
-      const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm);
-      full_tile_body(c, yc, e.P, e.part, e.nb, e.zpart, tile, tile, sm);
+      full_tile_of(e, tile, sm);
     }
     return;
   }
@@ -1058,9 +1615,7 @@ __global__ __launch_bounds__(256, 2) void k_force_full_batched(const BatchHdr *_
     if (i < 0) i += active;
     for (; i < cnt; i += active) {
       const int64_t tile = e.tlist[first + i];
-      float2 yc[16];
-      const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm);
-      full_tile_body(c, yc, e.P, e.part, e.nb, e.zpart, tile, tile, sm);
+      full_tile_of(e, tile, sm);
     }
     base += cnt;
   }
@@ -1079,7 +1634,7 @@ __global__ __launch_bounds__(256) void k_gather_batched(const BatchHdr *__restri
   gather_rows(e.Y, e.perm, e.n, e.yp, e.extent, b);
 }
 
-__global__ __launch_bounds__(kUpd) void k_update_batched(const BatchHdr *__restrict__ bh,
+__global__ __launch_bounds__(kUpd, 8) void k_update_batched(const BatchHdr *__restrict__ bh,
                                                         int count, int64_t tiles, int64_t blocks,
                                                         float alpha, float mu, float eta,
                                                         float min_gain, int lr_rule) {
@@ -1091,9 +1646,13 @@ __global__ __launch_bounds__(kUpd) void k_update_batched(const BatchHdr *__restr
   const BatchEntry &e = tab[p];
   const int64_t b = gb - e.blk0;
   if (b < 0 || b >= e.nb) return;
-  update_wg(e.part, e.slots, e.nslots, e.zpart, e.nt, e.n, e.nb, e.perm, e.Y, e.U, e.G, alpha, mu,
-            eta, min_gain, lr_rule, e.extent, nullptr, nullptr, e.meanpart, e.h,
-            (int)(b * kUpdPerBlock + blockIdx.x % kUpdPerBlock), sm);
+  const int wg = (int)(b * kUpdPerBlock + blockIdx.x % kUpdPerBlock);
+  if (e.split > 1)
+    update_units_wg(e.part, e.nz, e.zpart, e.nt, e.n, e.nb, e.perm, e.Y, e.U, e.G, alpha, mu, eta,
+                    min_gain, lr_rule, e.extent, nullptr, nullptr, e.meanpart, e.h, wg, sm);
+  else
+    update_wg(e.part, e.slots, e.nslots, e.zpart, e.nt, e.n, e.nb, e.perm, e.Y, e.U, e.G, alpha,
+              mu, eta, min_gain, lr_rule, e.extent, nullptr, nullptr, e.meanpart, e.h, wg, sm);
 }
 
 __global__ __launch_bounds__(256) void k_recentre_batched(const BatchHdr *__restrict__ bh,
@@ -1106,26 +1665,34 @@ __global__ __launch_bounds__(256) void k_recentre_batched(const BatchHdr *__rest
   const BatchEntry &e = tab[p];
   const int64_t b = (int64_t)blockIdx.x - e.blk0;
   if (b < 0 || b >= e.nb) return;
-  recentre_wg(e.meanpart, e.n, e.nb, e.Y, e.h, (int)b, smean);
+  recentre_wg(e.meanpart, e.n, mean_parts(e.nb, e.split), e.Y, e.h, (int)b, smean);
 }
 
 __global__ __launch_bounds__(kUpd) void k_grad_only(
     const float4 *__restrict__ part, const int32_t *__restrict__ slots,
-    const int32_t *__restrict__ nslots, const float *__restrict__ zpart, int64_t nt, int64_t n,
-    int32_t nb, const int32_t *__restrict__ perm, float alpha, float2 *__restrict__ grad_out,
+    const int32_t *__restrict__ nslots, const uint8_t *__restrict__ nz,
+    const float *__restrict__ zpart, int64_t nt, int64_t n, int32_t nb, int split,
+    const int32_t *__restrict__ perm, float alpha, float2 *__restrict__ grad_out,
     double *__restrict__ z_out, Hdr *h) {
   __shared__ UpdSmem sm;
   if (!state_ok(h, n)) return;
   const int wg = blockIdx.x, b = wg / kUpdPerBlock, t = threadIdx.x, q = t / kUpdRows;
   const int r = (wg % kUpdPerBlock) * kUpdRows + t % kUpdRows;
   const int64_t ir = (int64_t)b * T + r;
-  const double Z = z_total(zpart, nt, sm);
+  double Z;
+  double4 rs;
+  if (split > 1) {
+    rs = unit_sums(part, nz, zpart, nt, nb, b, r, q, Z, sm);
+  } else {
+    Z = z_total(zpart, nt, sm);
+    rs = row_sums(part, slots, nslots, nb, b, r, q, sm);
+  }
   if (wg == 0 && t == 0) {
     h->z = Z;
     if (z_out) *z_out = Z;
     if (!isfinite(Z) || !(Z > 0.0)) flag_error(h, kErrNonFinite);
   }
-  const float2 g = gradient_of(row_sums(part, slots, nslots, nb, b, r, q, sm), (double)alpha, Z);
+  const float2 g = gradient_of(rs, (double)alpha, Z);
   if (q == 0 && ir < n) {
     grad_out[perm[ir]] = g;
     if (!(isfinite(g.x) && isfinite(g.y))) flag_error(h, kErrNonFinite);
@@ -1335,7 +1902,19 @@ hipError_t side_stream(SideStream *&out) {
 }
 }  // namespace
 
+// The force pass of a split problem: one launch over its units.
+static hipError_t launch_force_units(const Layout &L, void *ws, const float *y, int32_t key,
+                                     hipStream_t st) {
+  hipLaunchKernelGGL(k_force_unit, dim3((unsigned)(L.nt * kUnits)), dim3(256), 0, st,
+                     at<const float4>(ws, L.P), reinterpret_cast<const float2 *>(y),
+                     at<const int32_t>(ws, L.perm), L.n, L.nb, at<float4>(ws, L.part),
+                     at<float>(ws, L.zpart), at<float4>(ws, L.extent), at<const int2>(ws, L.tmap),
+                     at<const uint8_t>(ws, L.nz), key, at<Hdr>(ws, L.hdr));
+  return hipGetLastError();
+}
+
 hipError_t launch_force(const Layout &L, void *ws, const float *y, hipStream_t st) {
+  if (L.split > 1) return launch_force_units(L, ws, y, -1, st);
   Hdr *h = at<Hdr>(ws, L.hdr);
   float2 *yp = at<float2>(ws, L.yp);
   hipLaunchKernelGGL(k_gather_y, dim3(L.nb), dim3(256), 0, st, reinterpret_cast<const float2 *>(y),
@@ -1344,6 +1923,11 @@ hipError_t launch_force(const Layout &L, void *ws, const float *y, hipStream_t s
   const int2 *tm = at<const int2>(ws, L.tmap);
   float4 *part = at<float4>(ws, L.part);
   float *zp = at<float>(ws, L.zpart);
+  if (L.nt <= kAnyTiles) {
+    hipLaunchKernelGGL(k_force_any, dim3((unsigned)L.nt), dim3(256), 0, st, at<const float4>(ws, L.P),
+                       (const float2 *)yp, L.n, L.nb, part, zp, tm, at<const uint8_t>(ws, L.nz), h);
+    return hipGetLastError();
+  }
   const unsigned full_grid = (unsigned)(L.nt < kFullGrid ? L.nt : kFullGrid);
   std::lock_guard<std::mutex> lock(g_side_mu);
   SideStream *ss = nullptr;
@@ -1368,6 +1952,13 @@ hipError_t launch_force(const Layout &L, void *ws, const float *y, hipStream_t s
 // The two write disjoint partial-sum slots. The slot lists and the sums of P
 // are those of the affinity stage.
 hipError_t launch_force_implicit(const Layout &L, void *ws, const float *y, hipStream_t st) {
+  if (L.split > 1) {
+    // the buffer holds the whole triangle (at most 136 tiles): one round
+    static_assert(kSplitNb * (kSplitNb + 1) / 2 <= kImplicitTiles, "a split problem fits");
+    hipError_t e = launch_implicit_tiles(L, ws, 0, L.nt, 0, true, true, st);
+    return e != hipSuccess ? e
+                           : launch_force_units(L, ws, y, implicit_key(L.d, L.mode), st);
+  }
   Hdr *h = at<Hdr>(ws, L.hdr);
   float2 *yp = at<float2>(ws, L.yp);
   hipLaunchKernelGGL(k_gather_y, dim3(L.nb), dim3(256), 0, st, reinterpret_cast<const float2 *>(y),
@@ -1436,16 +2027,23 @@ hipError_t launch_update(const Layout &L, void *ws, float *y, float *u, float *g
                          float *grad_out, double *z_out, hipStream_t st) {
   Hdr *h = at<Hdr>(ws, L.hdr);
   double2 *mp = at<double2>(ws, L.meanpart);
-  hipLaunchKernelGGL(k_update, dim3((unsigned)(L.nb * kUpdPerBlock)), dim3(kUpd), 0, st,
-                     at<const float4>(ws, L.part), at<const int32_t>(ws, L.slots),
-                     at<const int32_t>(ws, L.nslots), at<const float>(ws, L.zpart), L.nt, L.n,
-                     L.nb, at<const int32_t>(ws, L.perm), reinterpret_cast<float2 *>(y),
-                     reinterpret_cast<float2 *>(u), reinterpret_cast<float2 *>(g), alpha, mu, eta,
-                     min_gain, lr_rule, at<const float4>(ws, L.extent),
-                     reinterpret_cast<float2 *>(grad_out), z_out, mp, h);
+  const dim3 grid((unsigned)(L.nb * kUpdPerBlock));
+  float2 *fy = reinterpret_cast<float2 *>(y), *fu = reinterpret_cast<float2 *>(u),
+         *fg = reinterpret_cast<float2 *>(g), *go = reinterpret_cast<float2 *>(grad_out);
+  if (L.split > 1)
+    hipLaunchKernelGGL(k_update_units, grid, dim3(kUpd), 0, st, at<const float4>(ws, L.part),
+                       at<const uint8_t>(ws, L.nz), at<const float>(ws, L.zpart), L.nt, L.n, L.nb,
+                       at<const int32_t>(ws, L.perm), fy, fu, fg, alpha, mu, eta, min_gain,
+                       lr_rule, at<const float4>(ws, L.extent), go, z_out, mp, h);
+  else
+    hipLaunchKernelGGL(k_update, grid, dim3(kUpd), 0, st, at<const float4>(ws, L.part),
+                       at<const int32_t>(ws, L.slots), at<const int32_t>(ws, L.nslots),
+                       at<const float>(ws, L.zpart), L.nt, L.n, L.nb,
+                       at<const int32_t>(ws, L.perm), fy, fu, fg, alpha, mu, eta, min_gain,
+                       lr_rule, at<const float4>(ws, L.extent), go, z_out, mp, h);
   if (recentre)
     hipLaunchKernelGGL(k_recentre, dim3((unsigned)((L.n + 255) / 256)), dim3(256), 0, st, mp, L.n,
-                       L.nb, reinterpret_cast<float2 *>(y), h);
+                       mean_parts(L.nb, L.split), fy, h);
   return hipGetLastError();
 }
 
@@ -1454,8 +2052,9 @@ hipError_t launch_gradient_only(const Layout &L, void *ws, float alpha, float *g
   Hdr *h = at<Hdr>(ws, L.hdr);
   hipLaunchKernelGGL(k_grad_only, dim3((unsigned)(L.nb * kUpdPerBlock)), dim3(kUpd), 0, st,
                      at<const float4>(ws, L.part), at<const int32_t>(ws, L.slots),
-                     at<const int32_t>(ws, L.nslots), at<const float>(ws, L.zpart), L.nt, L.n,
-                     L.nb, at<const int32_t>(ws, L.perm), alpha,
+                     at<const int32_t>(ws, L.nslots), at<const uint8_t>(ws, L.nz),
+                     at<const float>(ws, L.zpart), L.nt, L.n, L.nb, L.split,
+                     at<const int32_t>(ws, L.perm), alpha,
                      reinterpret_cast<float2 *>(grad_out), z_out, h);
   return hipGetLastError();
 }
@@ -1472,47 +2071,64 @@ hipError_t launch_cost(const Layout &L, void *ws, const float *y, double *out, h
   return hipGetLastError();
 }
 
-hipError_t launch_batch_cost(const void *batch_ws, int count, int64_t total_tiles,
-                             int64_t total_blocks, double *out, hipStream_t st) {
+hipError_t launch_batch_cost(const void *batch_ws, int count, const BatchTotals &tot, double *out,
+                             hipStream_t st) {
   const BatchHdr *bh = reinterpret_cast<const BatchHdr *>(batch_ws);
-  hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)total_blocks), dim3(256), 0, st, bh, count,
-                     total_tiles, total_blocks);
-  hipLaunchKernelGGL(k_cost_batched, dim3((unsigned)total_tiles), dim3(256), 0, st, bh, count,
-                     total_tiles, total_blocks);
+  hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
+                     tot.tiles, tot.blocks);
+  hipLaunchKernelGGL(k_cost_batched, dim3((unsigned)tot.tiles), dim3(256), 0, st, bh, count,
+                     tot.tiles, tot.blocks);
   hipLaunchKernelGGL(k_cost_reduce_batched, dim3((unsigned)count), dim3(1024), 0, st, bh, count,
-                     total_tiles, total_blocks, out);
+                     tot.tiles, tot.blocks, out);
   return hipGetLastError();
 }
 
-hipError_t launch_batch_step(const void *batch_ws, int count, int64_t total_tiles,
-                             int64_t total_blocks, float alpha, float mu, float eta,
-                             float min_gain, int recentre, int lr_rule, hipStream_t st) {
+hipError_t launch_batch_step(const void *batch_ws, int count, const BatchTotals &tot, float alpha,
+                             float mu, float eta, float min_gain, int recentre, int lr_rule,
+                             hipStream_t st) {
   const BatchHdr *bh = reinterpret_cast<const BatchHdr *>(batch_ws);
-  hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)total_blocks), dim3(256), 0, st, bh, count,
-                     total_tiles, total_blocks);
-  {
+  if (tot.whole == 0) {
+    // split problems only: no gather, one force launch, one stream. Units per
+    // workgroup: a workgroup of more units reads its columns and finds its
+    // problem once for all of them, so as many as still leave two workgroups
+    // for every compute unit (4,800 units: 1 to a workgroup 110 us, 2: 80 us,
+    // 4: 66 us)
+    const int per = tot.units >= 4 * kFullGrid ? 4 : tot.units >= 2 * kFullGrid ? 2 : 1;
+    hipLaunchKernelGGL(k_force_unit_batched, dim3((unsigned)(tot.units / per)), dim3(256), 0, st,
+                       bh, count, tot.tiles, tot.blocks, tot.units, per);
+  } else {
+    hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
+                       tot.tiles, tot.blocks);
+  }
+  if (tot.whole > 0 && tot.tiles <= kAnyTilesBatched) {
+    hipLaunchKernelGGL(k_force_any_batched, dim3((unsigned)tot.tiles), dim3(256), 0, st, bh, count,
+                       tot.tiles, tot.blocks);
+  } else if (tot.whole > 0) {
     std::lock_guard<std::mutex> lock(g_side_mu);
     SideStream *ss = nullptr;
     hipError_t e = side_stream(ss);
     if (e != hipSuccess) return e;
     if ((e = hipEventRecord(ss->fork, st)) != hipSuccess) return e;
-    const unsigned full_grid = (unsigned)(total_tiles < kFullGrid ? total_tiles : kFullGrid);
-    hipLaunchKernelGGL(k_force_full_batched, dim3(full_grid), dim3(256), 0, st, bh, count,
-                       total_tiles, total_blocks);
+    const unsigned full_grid = (unsigned)(tot.tiles < kFullGrid ? tot.tiles : kFullGrid);
+    if (count <= kBatchLds)
+      hipLaunchKernelGGL(k_force_full_batched<false>, dim3(full_grid), dim3(256), 0, st, bh, count,
+                         tot.tiles, tot.blocks);
+    else
+      hipLaunchKernelGGL(k_force_full_batched<true>, dim3(full_grid), dim3(256), 0, st, bh, count,
+                         tot.tiles, tot.blocks);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(ss->s, ss->fork, 0)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_force_zero_batched, dim3((unsigned)total_tiles), dim3(256), 0, ss->s, bh,
-                       count, total_tiles, total_blocks);
+    hipLaunchKernelGGL(k_force_zero_batched, dim3((unsigned)tot.tiles), dim3(256), 0, ss->s, bh,
+                       count, tot.tiles, tot.blocks);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipEventRecord(ss->join, ss->s)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(st, ss->join, 0)) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_update_batched, dim3((unsigned)(total_blocks * kUpdPerBlock)), dim3(kUpd),
-                     0, st, bh, count,
-                     total_tiles, total_blocks, alpha, mu, eta, min_gain, lr_rule);
+  hipLaunchKernelGGL(k_update_batched, dim3((unsigned)(tot.blocks * kUpdPerBlock)), dim3(kUpd), 0,
+                     st, bh, count, tot.tiles, tot.blocks, alpha, mu, eta, min_gain, lr_rule);
   if (recentre)
-    hipLaunchKernelGGL(k_recentre_batched, dim3((unsigned)total_blocks), dim3(256), 0, st, bh,
-                       count, total_tiles, total_blocks);
+    hipLaunchKernelGGL(k_recentre_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
+                       tot.tiles, tot.blocks);
   return hipGetLastError();
 }
 
