@@ -13,59 +13,92 @@
 
 namespace {
 
-constexpr int kKdeThreads = 256;
-constexpr int kKdeCells = 4;  // cells per thread (consecutive along x)
+constexpr int kKdeTile = 32;     // raster tile of a workgroup: 32 x 32 cells
+constexpr int kKdeWaves = 16;    // waves of a workgroup, each a share of the points
+constexpr int kKdeStage = 64;    // points a wave stages at a time
+constexpr int kKdeChunk = 256;   // points summed in FP32 before their sum goes to FP64
 constexpr double kLog2e = 1.4426950408889634074;
 constexpr double kInvPi = 0.31830988618379067154;
 
-// One thread: kKdeCells consecutive cells of one raster row. Points pass
-// through LDS in chunks of 256 as {x, y, beta log2(e), beta / pi}; each cell
-// sums a chunk in FP32 and the chunk sums in FP64.
-__global__ __launch_bounds__(kKdeThreads) void k_kde_raster(const float2 *__restrict__ y,
-                                                            const double *__restrict__ beta,
-                                                            int64_t n, tsne_raster g,
-                                                            float *__restrict__ out) {
-  __shared__ float4 pts[kKdeThreads];
-  const int64_t per_row = (g.gx + kKdeCells - 1) / kKdeCells;
-  const int64_t slot = (int64_t)blockIdx.x * kKdeThreads + threadIdx.x;
-  const int64_t v = slot / per_row, u0 = (slot - v * per_row) * kKdeCells;
-  const bool live = v < g.gy;
-  const float cy = g.y0 + ((float)v + 0.5f) * g.cy;
-  float cx[kKdeCells];
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+struct KdeSmem {
+  union {
+    float4 pts[kKdeWaves][kKdeStage];                // {x, y, beta log2(e), beta / pi}
+    double sum[kKdeWaves][kKdeTile][kKdeTile];       // the waves' partial rasters
+  };
+};
+
+// The Gaussian of a point is the product of one along x and one along y, so
+// the raster is a contraction over the points,
+//   f(v, u) = sum_j [beta_j / pi exp(-beta_j (cy_v - y_j)^2)] exp(-beta_j (cx_u - x_j)^2),
+// which v_mfma_f32_32x32x2_f32 forms: two points a step, lane l supplying the
+// factors of point l / 32 for row v = l % 32 (A) and column u = l % 32 (B), and
+// receiving cells (8 (r / 4) + 4 (l / 32) + r % 4, l % 32), r = 0 .. 15. A step
+// is two exponentials per lane for 2,048 cell terms, where a sum over the
+// cells takes one exponential each. What bounds it: the two exponentials and
+// seven other instructions (60 issue cycles) against the 64 cycles of the MFMA,
+// on the four waves of a SIMD. 65,536 points on 512 x 512 cells: 0.395 ms
+// (4.3e13 cell terms a second) against 3.74 ms for one exponential per term.
+// A workgroup covers one tile; its waves share the points in contiguous
+// pieces, so that a small raster still fills its compute units. As before, 256
+// points are summed in FP32 and the chunk sums in FP64; the waves' sums meet in
+// LDS in wave order.
+__global__ __launch_bounds__(64 * kKdeWaves) void k_kde_raster(const float2 *__restrict__ y,
+                                                               const double *__restrict__ beta,
+                                                               int64_t n, tsne_raster g,
+                                                               float *__restrict__ out) {
+  __shared__ KdeSmem sm;
+  const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 31, lk = l >> 5;
+  const unsigned across = (unsigned)((g.gx + kKdeTile - 1) / kKdeTile);
+  const int64_t u0 = (int64_t)(blockIdx.x % across) * kKdeTile,
+                v0 = (int64_t)(blockIdx.x / across) * kKdeTile;
+  const float cx = g.x0 + ((float)(u0 + li) + 0.5f) * g.cx;
+  const float cy = g.y0 + ((float)(v0 + li) + 0.5f) * g.cy;
+  // this wave's points: whole chunks
+  const int64_t chunks = (n + kKdeChunk - 1) / kKdeChunk;
+  const int64_t c0 = chunks * w / kKdeWaves, c1 = chunks * (w + 1) / kKdeWaves;
+  double acc[16];
 #pragma unroll
-  for (int k = 0; k < kKdeCells; ++k) cx[k] = g.x0 + ((float)(u0 + k) + 0.5f) * g.cx;
-  double acc[kKdeCells] = {};
-  for (int64_t j0 = 0; j0 < n; j0 += kKdeThreads) {
-    __syncthreads();
-    const int64_t j = j0 + threadIdx.x;
-    if (j < n) {
-      const float2 p = y[j];
-      const double b = beta[j];
-      pts[threadIdx.x] = make_float4(p.x, p.y, (float)(b * kLog2e), (float)(b * kInvPi));
-    } else {
-      pts[threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);  // weight 0
-    }
-    __syncthreads();
-    const int cnt = (int)((n - j0) < kKdeThreads ? (n - j0) : kKdeThreads);
-    float s[kKdeCells] = {};
-    for (int q = 0; q < cnt; ++q) {
-      const float4 p = pts[q];
-      const float dy = cy - p.y, dy2 = dy * dy;
-#pragma unroll
-      for (int k = 0; k < kKdeCells; ++k) {
-        const float dx = cx[k] - p.x;
-        const float r2 = fmaf(dx, dx, dy2);
-        s[k] = fmaf(p.w, __builtin_amdgcn_exp2f(-p.z * r2), s[k]);
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0;
+  float4 *pts = sm.pts[w];
+  auto fetch = [&](int64_t j) {  // points past the end: weight 0
+    const float2 p = j < n ? y[j] : make_float2(0.f, 0.f);
+    const double b = j < n ? beta[j] : 0.0;
+    return make_float4(p.x, p.y, (float)(b * kLog2e), (float)(b * kInvPi));
+  };
+  float4 next = c0 < c1 ? fetch(c0 * kKdeChunk + l) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int64_t c = c0; c < c1; ++c) {
+    v16f s = {};
+#pragma unroll 1
+    for (int q = 0; q < kKdeChunk; q += kKdeStage) {
+      // one wave writes and reads this buffer: no barrier between waves
+      __builtin_amdgcn_wave_barrier();
+      pts[l] = next;
+      __builtin_amdgcn_wave_barrier();
+      next = fetch(c * kKdeChunk + q + kKdeStage + l);  // in flight over this stage
+#pragma unroll 8
+      for (int k = 0; k < kKdeStage; k += 2) {
+        const float4 p = pts[k + lk];
+        const float dx = cx - p.x, dy = cy - p.y;
+        const float ey = p.w * __builtin_amdgcn_exp2f(-p.z * (dy * dy));
+        const float ex = __builtin_amdgcn_exp2f(-p.z * (dx * dx));
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(ey, ex, s, 0, 0, 0);
       }
     }
 #pragma unroll
-    for (int k = 0; k < kKdeCells; ++k) acc[k] += (double)s[k];
+    for (int r = 0; r < 16; ++r) acc[r] += (double)s[r];
   }
-  if (!live) return;
-  const double scale = (double)g.cx * (double)g.cy / (double)n;
+  __syncthreads();  // the staged points give way to the sums
 #pragma unroll
-  for (int k = 0; k < kKdeCells; ++k)
-    if (u0 + k < g.gx) out[v * g.gx + u0 + k] = (float)(acc[k] * scale);
+  for (int r = 0; r < 16; ++r) sm.sum[w][8 * (r >> 2) + 4 * lk + (r & 3)][li] = acc[r];
+  __syncthreads();
+  const int64_t v = v0 + (t >> 5), u = u0 + (t & 31);
+  if (v >= g.gy || u >= g.gx) return;
+  double f = 0.0;
+#pragma unroll
+  for (int q = 0; q < kKdeWaves; ++q) f += sm.sum[q][t >> 5][t & 31];
+  out[v * g.gx + u] = (float)(f * ((double)g.cx * (double)g.cy / (double)n));
 }
 
 }  // namespace
@@ -74,10 +107,11 @@ namespace tsne {
 
 hipError_t launch_kde_raster(const float *y, int64_t n, const double *beta, const tsne_raster &g,
                              float *out, hipStream_t st) {
-  const int64_t slots = (int64_t)g.gy * ((g.gx + kKdeCells - 1) / kKdeCells);
-  hipLaunchKernelGGL(k_kde_raster, dim3((unsigned)((slots + kKdeThreads - 1) / kKdeThreads)),
-                     dim3(kKdeThreads), 0, st, reinterpret_cast<const float2 *>(y), beta, n, g,
-                     out);
+  static_assert(sizeof(KdeSmem) <= 160 * 1024, "one workgroup per compute unit");
+  const int64_t tiles = (((int64_t)g.gx + kKdeTile - 1) / kKdeTile) *
+                        (((int64_t)g.gy + kKdeTile - 1) / kKdeTile);
+  hipLaunchKernelGGL(k_kde_raster, dim3((unsigned)tiles), dim3(64 * kKdeWaves), 0, st,
+                     reinterpret_cast<const float2 *>(y), beta, n, g, out);
   return hipGetLastError();
 }
 
