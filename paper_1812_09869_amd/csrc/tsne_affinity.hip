@@ -1842,8 +1842,9 @@ __global__ __launch_bounds__(256) void k_slot_lists(const uint8_t *__restrict__ 
 // scheme). Same method as above with one wave per row: the row's squared
 // distances (FP64 direct differences, rounded to FP32 like the distance
 // block of the large path) stay in registers for the bisection, whose sums
-// are wave reductions, so no workgroup barrier sits inside the search. The
-// rows of a workgroup belong to one problem and share the staging of
+// are wave reductions, so no workgroup barrier sits inside the search (several
+// rows to a wave where they fit, see k_small_calibrate). The rows of a
+// workgroup belong to one problem and share the staging of
 // the other points' coordinates in LDS. The distances of tiles (I, J >= I)
 // go straight into the P store in consumer order; the pack, reduction and
 // list steps are the same device code as the single-problem path.
@@ -1895,28 +1896,83 @@ __global__ __launch_bounds__(256) void k_small_init(const SmallEntry *__restrict
   e.inv[i] = (int32_t)i;
 }
 
-template <int VPT>
-__global__ __launch_bounds__(kSmallRows * 64) void k_small_calibrate(
+// Sums over the wave of R rows' values. R = 1: the butterfly of wave_sum_d,
+// every lane with the total. R = 4: lane l ends with the total of row l / 16;
+// the first two levels (distances 32 and 16) exchange whole rows between the
+// halves with the lane-swap instructions, each halving the rows a lane carries,
+// and the last four rotate inside the 16 lanes. The additions are the
+// butterfly's, in its order (operands swapped at most), so the totals are too.
+__device__ __forceinline__ double swap32_add(double x, double y) {
+  const int2 a = __builtin_bit_cast(int2, x), b = __builtin_bit_cast(int2, y);
+  const auto lo = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
+         __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+__device__ __forceinline__ double swap16_add(double x, double y) {
+  const int2 a = __builtin_bit_cast(int2, x), b = __builtin_bit_cast(int2, y);
+  const auto lo = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
+         __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+  const int2 a = __builtin_bit_cast(int2, x);
+  return x + __builtin_bit_cast(
+                 double, make_int2(__builtin_amdgcn_mov_dpp(a.x, CTRL, 0xf, 0xf, true),
+                                   __builtin_amdgcn_mov_dpp(a.y, CTRL, 0xf, 0xf, true)));
+}
+template <int R>
+__device__ __forceinline__ double rows_sum_d(const double (&x)[R]) {
+  if constexpr (R == 1) {
+    return wave_sum_d(x[0]);
+  } else {
+    // lower half rows 0, 1, upper half rows 2, 3; then one row to 16 lanes
+    double v = swap16_add(swap32_add(x[0], x[2]), swap32_add(x[1], x[3]));
+    v = dpp_add<0x128>(v);
+    v = dpp_add<0x124>(v);
+    v = dpp_add<0x122>(v);
+    return dpp_add<0x121>(v);
+  }
+}
+
+// R rows to a wave. What bounds a pass over 1,000 points is not its 16
+// exponentials a lane but the three wave sums, the logarithm and the divisions
+// in FP64, which every lane repeats for the one row; and in the distances one
+// read of a double per lane feeds two FP64 instructions, which is the LDS rate.
+// With four rows the wave reduces all their sums together and takes their four
+// steps in the four groups of 16 lanes at once, and a read of a pair of
+// coordinates (ds_read_b128; the row stride is twice an odd number of doubles,
+// which spreads 16 lanes over all banks) feeds sixteen instructions. Every
+// row's sums and steps are those of R = 1, so its results are too. 120,000 rows
+// of 1,000 points in 30 dimensions, perplexity 400: 2.25 ms with one row to a
+// wave, 2.32 with four rows and four separate steps, 1.62 this way, 1.12 with
+// the start below. Four rows up to 1,024 points, one above, where two rows'
+// distances no longer stay in registers.
+template <int VPT, int R>
+__global__ __launch_bounds__(kSmallWaves * 64) void k_small_calibrate(
     const SmallEntry *__restrict__ tab, int count, int32_t dstride, int max_bisect,
     double tol_h) {
   // LDS (FP64, converted once): two buffers of 64 points ([64][dstride]
-  // each), then the own rows
-  extern __shared__ double sx[];
-  constexpr int kThr = kSmallRows * 64;
+  // each), then the own rows; the columns past d are zero
+  extern __shared__ __align__(16) double sx[];
+  constexpr int kThr = kSmallWaves * 64;
+  constexpr int kRows = kSmallWaves * R;
   constexpr int kPre = 64 * kSmallMaxD / kThr;  // prefetch registers per thread
   const int p = small_find(tab, count, blockIdx.x, 0);
   const SmallEntry &e = tab[p];
   const int64_t n = e.n;
   const int32_t d = e.d;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int64_t r0 = ((int64_t)blockIdx.x - e.wg0) * kSmallRows;
-  const int64_t i = r0 + w;
-  const bool row_ok = i < n;
+  const int64_t r0 = ((int64_t)blockIdx.x - e.wg0) * kRows;
+  const int64_t i0 = r0 + R * w;  // the wave's rows i0 .. i0 + R - 1
   double *own = sx + 2 * 64 * dstride;
-  for (int q = threadIdx.x; q < kSmallRows * d; q += kThr) {
-    const int rr = q / d, k = q - rr * d;
-    own[rr * dstride + k] = (r0 + rr) < n ? (double)e.x[(r0 + rr) * d + k] : 0.0;
+  for (int q = threadIdx.x; q < (2 * 64 + kRows) * dstride; q += kThr) {
+    const int rr = q / dstride - 2 * 64, k = q % dstride;
+    sx[q] = rr >= 0 && k < d && r0 + rr < n ? (double)e.x[(r0 + rr) * d + k] : 0.0;
   }
+  __syncthreads();
   const int nchunk = (int)((n + 63) / 64);
   // chunk c holds points 64c .. 64c + 63 as rows of d floats (contiguous in x)
   auto fetch = [&](int c, float (&pre)[kPre]) {
@@ -1927,14 +1983,19 @@ __global__ __launch_bounds__(kSmallRows * 64) void k_small_calibrate(
       pre[u] = (idx < 64 * d && idx < lim) ? e.x[base + idx] : 0.f;
     }
   };
+  // (row, coordinate) of this thread's first value and of the step between two
+  const int rr0 = threadIdx.x / d, k0 = threadIdx.x - rr0 * d, rs = kThr / d, ks = kThr - rs * d;
   auto put = [&](int c, const float (&pre)[kPre]) {
     double *buf = sx + (c & 1) * 64 * dstride;
+    int rr = rr0, k = k0;
 #pragma unroll
     for (int u = 0; u < kPre; ++u) {
-      const int idx = threadIdx.x + u * kThr;
-      if (idx < 64 * d) {
-        const int rr = idx / d, k = idx - rr * d;
-        buf[rr * dstride + k] = (double)pre[u];
+      if (rr < 64) buf[rr * dstride + k] = (double)pre[u];
+      rr += rs;
+      k += ks;
+      if (k >= d) {
+        k -= d;
+        ++rr;
       }
     }
   };
@@ -1942,67 +2003,128 @@ __global__ __launch_bounds__(kSmallRows * 64) void k_small_calibrate(
   fetch(0, pre);
   put(0, pre);
   __syncthreads();
-  const int I = (int)(i / T), il = (int)(i - (int64_t)I * T);
-  float v[VPT];
-  bool bad = false;
+  float v[R][VPT];
+  bool bad[R] = {};
 #pragma unroll
   for (int q = 0; q < VPT; ++q) {
-    v[q] = INFINITY;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r][q] = INFINITY;
     if (q < nchunk) {  // uniform over the workgroup
       if (q + 1 < nchunk) fetch(q + 1, pre);  // in flight while this chunk is used
       const int64_t j = (int64_t)q * 64 + l;
-      if (row_ok && j < n) {
-        double acc = 0.0;
-        const double *xj = sx + (q & 1) * 64 * dstride + l * dstride, *xi = own + w * dstride;
-        for (int k = 0; k < d; ++k) {
-          const double df = xj[k] - xi[k];
-          acc = fma(df, df, acc);
+      if (i0 < n) {
+        double acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = 0.0;
+        const double2 *xj = reinterpret_cast<const double2 *>(sx + (q & 1) * 64 * dstride +
+                                                              l * dstride);
+        const double2 *xi = reinterpret_cast<const double2 *>(own + R * w * dstride);
+        const int half = dstride / 2;
+        // pairs of coordinates; past d both sides are zero
+        for (int k = 0; k < (d + 1) / 2; ++k) {
+          const double2 a = xj[k];
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const double2 c = xi[r * half + k];
+            const double d0 = a.x - c.x, d1 = a.y - c.y;
+            acc[r] = fma(d0, d0, acc[r]);
+            acc[r] = fma(d1, d1, acc[r]);
+          }
         }
-        const float dv = (float)acc;
-        bad |= !isfinite(dv);
-        const int J = (int)(j / T);
-        if (J >= I) {
-          const int jl = (int)(j - (int64_t)J * T);
-          float *tp = reinterpret_cast<float *>(e.P + (size_t)(tile_start(I, e.nb) + (J - I)) * TT4);
-          tp[small_pos(il, jl)] = dv;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int64_t i = i0 + r;
+          if (i < n && j < n) {
+            const float dv = (float)acc[r];
+            bad[r] |= !isfinite(dv);
+            const int I = (int)(i / T), J = (int)(j / T);
+            if (J >= I) {
+              float *tp =
+                  reinterpret_cast<float *>(e.P + (size_t)(tile_start(I, e.nb) + (J - I)) * TT4);
+              tp[small_pos((int)(i - (int64_t)I * T), (int)(j - (int64_t)J * T))] = dv;
+            }
+            if (j != i) v[r][q] = dv;
+          }
         }
-        if (j != i) v[q] = dv;
       }
       if (q + 1 < nchunk) put(q + 1, pre);  // the other buffer: last read two chunks ago
       __syncthreads();
     }
   }
-  if (!row_ok) return;  // no barrier below this point
-  float mn = INFINITY;
-#pragma unroll
-  for (int q = 0; q < VPT; ++q) mn = fminf(mn, v[q]);
-  const float m = wave_min_f(mn);
-#pragma unroll
-  for (int q = 0; q < VPT; ++q) v[q] = (v[q] == INFINITY) ? kBig : v[q] - m;
+  if (i0 >= n) return;  // no barrier below this point
   const double logu = log(e.perplexity);
-  double beta = 1.0, lo = 0.0, hi = INFINITY, S = 0.0, H = 0.0;
-  float a = 0.f;
-  int it = 0, done = 0;
-  while (!done) {
-    ++it;
-    a = fmaxf((float)(beta * kLog2e), 1e-30f);
-    float s = 0.f, tt = 0.f, qq = 0.f;
+  // From here lane l holds the search of row i0 + g, g = l / 16 (R = 4), or of
+  // the one row (R = 1): the FP64 arithmetic of a step, several times the
+  // exponentials of 16 points a lane, is done once for all rows of the wave.
+  static_assert(R == 1 || R == 4, "a row to 16 lanes, or one row");
+  const int g = R == 4 ? l >> 4 : 0;
+  float m = 0.f;
 #pragma unroll
-    for (int q = 0; q < VPT; ++q) {
-      const float ex = __builtin_amdgcn_exp2f(-a * v[q]);
-      const float ve = v[q] * ex;  // 0 for an excluded entry (ex = 0)
-      s += ex;
-      tt += ve;
-      qq = fmaf(v[q], ve, qq);
+  for (int r = 0; r < R; ++r) {
+    float mn = INFINITY;
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) mn = fminf(mn, v[r][q]);
+    mn = wave_min_f(mn);
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) v[r][q] = (v[r][q] == INFINITY) ? kBig : v[r][q] - mn;
+    if (r == g) m = mn;
+  }
+  // Start of the search: at beta = 0 the entropy is ln(n - 1), its slope is
+  // zero and its curvature -Var(d), so it falls to ln u near
+  // beta = sqrt(2 ln((n - 1) / u) / Var(d)); one pass without exponentials. (From
+  // beta = 1, partial problems of 1,000 points at perplexity 400 took 13 passes,
+  // most of them halvings; from here 4.)
+  double beta, lo = 0.0, hi = INFINITY, S = 0.0, H = 0.0;
+  {
+    double T1[R], T2[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float t1 = 0.f, t2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < VPT; ++q) {
+        const float x = v[r][q] < kBig ? v[r][q] : 0.f;  // 0 for an excluded entry
+        t1 += x;
+        t2 = fmaf(x, x, t2);
+      }
+      T1[r] = (double)t1;
+      T2[r] = (double)t2;
     }
-    // butterfly sums: every lane holds the same totals, so the search below
-    // takes the same branch in every lane
-    const double SS = wave_sum_d((double)s), TT = wave_sum_d((double)tt);
-    const double QQ = wave_sum_d((double)qq);
+    const double cnt = (double)(n - 1), mean = rows_sum_d<R>(T1) / cnt;
+    const double var = rows_sum_d<R>(T2) / cnt - mean * mean;
+    beta = sqrt(2.0 * (log(cnt) - logu) / var);
+    if (!(beta > 0.0) || !isfinite(beta)) beta = 1.0;
+  }
+  float a = 0.f;
+  int it = 0, done = i0 + g < n ? 0 : 1;  // rows past the end have no search
+  while (!__all(done)) {
+    // a row that has stopped goes along with its last beta, unused
+    if (!done) {
+      ++it;
+      a = fmaxf((float)(beta * kLog2e), 1e-30f);
+    }
+    double SS[R], TT[R], QQ[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 16 * r));
+      float s = 0.f, tt = 0.f, qq = 0.f;
+#pragma unroll
+      for (int q = 0; q < VPT; ++q) {
+        const float ex = __builtin_amdgcn_exp2f(-ar * v[r][q]);
+        const float ve = v[r][q] * ex;  // 0 for an excluded entry (ex = 0)
+        s += ex;
+        tt += ve;
+        qq = fmaf(v[r][q], ve, qq);
+      }
+      SS[r] = (double)s;
+      TT[r] = (double)tt;
+      QQ[r] = (double)qq;
+    }
+    const double ss = rows_sum_d<R>(SS), ts = rows_sum_d<R>(TT), qs = rows_sum_d<R>(QQ);
+    if (done) continue;
     const double beff = (double)a * kLn2;
-    S = SS;
-    const double mean = TT / SS;
-    H = log(SS) + beff * mean;
+    S = ss;
+    const double mean = ts / ss;
+    H = log(ss) + beff * mean;
     if (fabs(H - logu) <= tol_h) {
       done = 1;
     } else if (isfinite(hi) && (hi - lo) <= hi * 0x1p-24) {
@@ -2018,7 +2140,7 @@ __global__ __launch_bounds__(kSmallRows * 64) void k_small_calibrate(
         lo = beta;
       else
         hi = beta;
-      const double var = QQ / SS - mean * mean;
+      const double var = qs / ss - mean * mean;
       const double nb = beta + (H - logu) / (beff * var);
       if (var > 0.0 && nb > lo && nb < hi && isfinite(nb))
         beta = nb;
@@ -2026,8 +2148,14 @@ __global__ __launch_bounds__(kSmallRows * 64) void k_small_calibrate(
         beta = isinf(hi) ? 2.0 * beta : 0.5 * (lo + hi);
     }
   }
-  bad = __any(bad);
-  if (l == 0) {
+  bool any_bad = false;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool ab = __any(bad[r]);
+    if (r == g) any_bad = ab;
+  }
+  const int64_t i = i0 + g;
+  if ((R == 4 ? (l & 15) : l) == 0 && i < n) {
     e.beta[i] = (double)a * kLn2;
     e.S[i] = S;
     e.H[i] = H;
@@ -2036,7 +2164,7 @@ __global__ __launch_bounds__(kSmallRows * 64) void k_small_calibrate(
     e.r[i] = (float)(1.0 / (2.0 * (double)n * S));
     e.evals[i] = done == 1 ? it : -it;
     if (done != 1) flag_error(e.h, kErrNoConv);
-    if (bad || !isfinite(H) || !isfinite(S)) flag_error(e.h, kErrNonFinite);
+    if (any_bad || !isfinite(H) || !isfinite(S)) flag_error(e.h, kErrNonFinite);
   }
 }
 
@@ -2501,24 +2629,29 @@ hipError_t launch_affinities_small(const SmallEntry *tab, int count, int64_t wgs
                                    int64_t blocks, int64_t nmax, int32_t dmax, int max_bisect,
                                    double tol_h, hipStream_t st) {
   if (nmax > kSmallMaxN || dmax > kSmallMaxD || count < 1) return hipErrorInvalidValue;
-  const int32_t dstride = dmax | 1;  // odd row stride: conflict-free LDS reads
-  const size_t lds = (size_t)(2 * 64 + kSmallRows) * dstride * sizeof(double);
+  // row stride in doubles: twice an odd number (16-byte aligned pairs, 16
+  // lanes' pairs in different banks)
+  const int32_t dstride = 2 * (((dmax + 1) / 2) | 1);
+  const int rows = small_rows(nmax);
+  const size_t lds = (size_t)(2 * 64 + rows) * dstride * sizeof(double);
   hipLaunchKernelGGL(k_small_init, dim3((unsigned)blocks), dim3(256), 0, st, tab, count);
-  const dim3 g((unsigned)wgs), b(kSmallRows * 64);
+  const dim3 g((unsigned)wgs), b(kSmallWaves * 64);
   const int vpt = (int)((nmax + 63) / 64);
+#define TSNE_SMALL(V, R)                                                                        \
+  hipLaunchKernelGGL((k_small_calibrate<V, R>), g, b, lds, st, tab, count, dstride, max_bisect, \
+                     tol_h)
+  // (rows to a wave as in small_rows)
   if (vpt <= 4)
-    hipLaunchKernelGGL(k_small_calibrate<4>, g, b, lds, st, tab, count, dstride, max_bisect, tol_h);
+    TSNE_SMALL(4, 4);
   else if (vpt <= 8)
-    hipLaunchKernelGGL(k_small_calibrate<8>, g, b, lds, st, tab, count, dstride, max_bisect, tol_h);
+    TSNE_SMALL(8, 4);
   else if (vpt <= 16)
-    hipLaunchKernelGGL(k_small_calibrate<16>, g, b, lds, st, tab, count, dstride, max_bisect,
-                       tol_h);
+    TSNE_SMALL(16, 4);
   else if (vpt <= 32)
-    hipLaunchKernelGGL(k_small_calibrate<32>, g, b, lds, st, tab, count, dstride, max_bisect,
-                       tol_h);
+    TSNE_SMALL(32, 1);
   else
-    hipLaunchKernelGGL(k_small_calibrate<64>, g, b, lds, st, tab, count, dstride, max_bisect,
-                       tol_h);
+    TSNE_SMALL(64, 1);
+#undef TSNE_SMALL
   hipLaunchKernelGGL(k_small_pack, dim3((unsigned)tiles), dim3(256), 0, st, tab, count);
   hipLaunchKernelGGL(k_small_slots, dim3((unsigned)blocks), dim3(256), 0, st, tab, count);
   hipLaunchKernelGGL(k_small_lists, dim3((unsigned)count), dim3(1024), 0, st, tab);

@@ -83,7 +83,7 @@ bool make_pt_layout(int64_t n, int32_t d, const tsne_pt_opts &o, PtLayout &P) {
   if (P.small) {
     for (int64_t s : P.z) {
       const tsne::Layout L = tsne::make_layout(s, d, TSNE_DIST_FP64);
-      P.small_wgs += (s + tsne::kSmallRows - 1) / tsne::kSmallRows;
+      P.small_wgs += (s + tsne::small_rows(P.zmax) - 1) / tsne::small_rows(P.zmax);
       P.small_tiles += L.nt;
       P.small_blocks += L.nb;
     }
@@ -174,15 +174,15 @@ int check_ws(void *ws, size_t bytes, const PtLayout &P) {
   return TSNE_OK;
 }
 
-// Prefix offsets of the small-problem table (first workgroup of kSmallRows rows,
+// Prefix offsets of the small-problem table (first workgroup of `rows` rows,
 // first tile, first row block of each problem); the totals are the layout's.
-void small_prefix(std::vector<tsne::SmallEntry> &tab) {
+void small_prefix(std::vector<tsne::SmallEntry> &tab, int rows) {
   int64_t w = 0, t = 0, b = 0;
   for (auto &e : tab) {
     e.wg0 = w;
     e.tile0 = t;
     e.blk0 = b;
-    w += (e.n + tsne::kSmallRows - 1) / tsne::kSmallRows;
+    w += (e.n + rows - 1) / rows;
     t += e.nt;
     b += e.nb;
   }
@@ -409,7 +409,7 @@ TSNE_API int tsne_pt_init(int64_t n, int32_t d, const tsne_pt_opts *opts, void *
       tsne::small_entry(L, at<char>(ws, P.ws[k]), at<float>(ws, P.xk) + P.row0[k] * d,
                         opts->perplexity, tab[k]);
     }
-    small_prefix(tab);
+    small_prefix(tab, tsne::small_rows(P.zmax));
     e = hipMemcpyAsync(at<char>(ws, P.smalltab), tab.data(), tab.size() * sizeof(tab[0]),
                        hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
