@@ -10,6 +10,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "tsne_internal.h"
 
 namespace tsne {
@@ -44,6 +46,15 @@ __device__ inline float wave_min_f(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// x plus the x of another lane of its row of 16 (a DPP control).
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+  const int2 a = __builtin_bit_cast(int2, x);
+  return x + __builtin_bit_cast(
+                 double, make_int2(__builtin_amdgcn_mov_dpp(a.x, CTRL, 0xf, 0xf, true),
+                                   __builtin_amdgcn_mov_dpp(a.y, CTRL, 0xf, 0xf, true)));
 }
 
 // ----------------------------------------------------------------------------
@@ -1558,6 +1569,301 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_keys(
   }
 }
 
+// ----------------------------------------------------------------------------
+// The same tree for d <= kTreeRowD, from the input rows themselves. The kernels
+// above read the centred X by column through the order, 8 bytes from each
+// cache line and each row twice per power iteration, and a level of a small
+// problem is eleven launches and a sort. Here 16 lanes share a row (Q of its
+// coordinates each, in registers from one contiguous read), so a power
+// iteration is one sweep: the row's product with the direction is a sum over
+// the 16 lanes, and the row times it goes into the lanes' accumulators. The
+// arithmetic is FP64 as above, in another order of summation, so the
+// projections round to the same FP32 keys but for one in about 10^8.
+// A segment of at most kSegRows rows is one workgroup for its whole level: mean,
+// power iterations, projections, an LDS sort of (projection, position) in one
+// 64-bit word, the new order. n = 2,000, d = 10: 44 us a level (5 of them each
+// power iteration, 13 the sort) against 110 for its launches; 65,536 x 50: 1.9
+// ms for all eight levels against 4.7.
+// ----------------------------------------------------------------------------
+constexpr int kTreeRowD = 128;
+constexpr int kSegRows = 4096;
+constexpr int kSegThreads = 1024;
+
+// Q coordinates (tc + 16 q) of one row, zero past d.
+template <int Q>
+__device__ __forceinline__ void row_coords(const float *__restrict__ x, int64_t i, int32_t d,
+                                           int tc, float (&c)[Q]) {
+  const float *xr = x + i * d;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) c[q] = tc + 16 * q < d ? xr[tc + 16 * q] : 0.f;
+}
+
+// Sum over the 16 lanes of a row group, the same in every lane.
+__device__ __forceinline__ double rot16_sum_d(double v) {
+  v = dpp_add<0x128>(v);
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x122>(v);
+  return dpp_add<0x121>(v);
+}
+
+// fn(r, coordinates) for rows first, first + step, ... < r1 (a row to 16 lanes,
+// at(r) its point), with the reads of four rows in flight (16 made no difference).
+template <int Q, class At, class Fn>
+__device__ __forceinline__ void tree_rows(const float *__restrict__ x, int32_t d, int64_t first,
+                                          int64_t r1, int step, int tc, At at, Fn fn) {
+  constexpr int U = Q > 4 ? 2 : 4;
+  for (int64_t r = first; r < r1; r += U * step) {
+    int64_t i[U];
+    float c[U][Q];
+#pragma unroll
+    for (int u = 0; u < U; ++u) i[u] = at(r + u * step < r1 ? r + u * step : r);
+#pragma unroll
+    for (int u = 0; u < U; ++u) row_coords<Q>(x, i[u], d, tc, c[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r + u * step < r1) fn(r + u * step, i[u], c[u]);
+  }
+}
+
+// One sweep, x being centred by the column means gm first. POWER: acc += (x -
+// mean) ((x - mean) . v), else acc += x.
+template <int Q, bool POWER, class At>
+__device__ __forceinline__ void tree_sweep(const float *__restrict__ x, int32_t d, int64_t first,
+                                           int64_t r1, int step, int tc, At at,
+                                           const double (&gm)[Q], const double (&mean)[Q],
+                                           const double (&v)[Q], double (&acc)[Q]) {
+#pragma unroll
+  for (int q = 0; q < Q; ++q) acc[q] = 0.0;
+  tree_rows<Q>(x, d, first, r1, step, tc, at, [&](int64_t, int64_t, float (&c)[Q]) {
+    if (POWER) {
+      double e[Q], w = 0.0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        e[q] = ((double)c[q] - gm[q]) - mean[q];
+        w = fma(e[q], v[q], w);  // v is zero past d
+      }
+      w = rot16_sum_d(w);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc[q] = fma(e[q], w, acc[q]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc[q] += (double)c[q] - gm[q];
+    }
+  });
+}
+
+// Sums of acc over the workgroup's row groups into out[0 .. d) (LDS, FP64, a
+// fixed order). W waves.
+template <int Q, int W>
+__device__ __forceinline__ void tree_gather(const double (&acc)[Q], int32_t d, int tc,
+                                            double (*red)[kTreeRowD], double *out) {
+  const int t = threadIdx.x, w = t >> 6, l = t & 63;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    double s = acc[q];
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if (l < 16) red[w][tc + 16 * q] = s;
+  }
+  __syncthreads();
+  if (t < d) {
+    double s = 0.0;
+    for (int g = 0; g < W; ++g) s += red[g][t];
+    out[t] = s;
+  }
+  __syncthreads();
+}
+
+// Start direction: fixed and the same for every segment.
+__device__ __forceinline__ double tree_start(int k) {
+  const uint32_t hsh = (uint32_t)(k + 1) * 2654435761u;
+  return 0.5 + (double)(hsh >> 8) * (1.0 / 16777216.0);
+}
+
+// 1 / |v| (0 for a zero vector: coincident points keep their order), by one wave.
+__device__ __forceinline__ double tree_scale(const double *v, int32_t d) {
+  double ss = 0.0;
+  for (int k = threadIdx.x & 63; k < d; k += 64) ss += v[k] * v[k];
+  ss = wave_sum_d(ss);
+  return ss > 0.0 ? 1.0 / sqrt(ss) : 0.0;
+}
+
+template <int Q>
+__global__ __launch_bounds__(kSegThreads) void k_tree_seg(const float *__restrict__ x,
+                                                          const double *__restrict__ gmean,
+                                                          int32_t d, int64_t n, int32_t nb,
+                                                          int level, int32_t *__restrict__ perm) {
+  constexpr int W = kSegThreads / 64;
+  __shared__ double red[W][kTreeRowD];
+  __shared__ double mean_s[kTreeRowD], v_s[kTreeRowD];
+  __shared__ uint64_t key[kSegRows];
+  __shared__ int32_t point[kSegRows];  // the segment's order
+  __shared__ double scale_s;
+  const int t = threadIdx.x, tc = t & 15;
+  const int64_t s = blockIdx.x;
+  const TreeSeg g = tree_segment(s, level, nb, n);
+  const int len = (int)(g.hi - g.lo);
+  if (len <= T || len > kSegRows) return;  // leaves are not split; the host sends no longer ones
+  for (int e = t; e < len; e += kSegThreads) point[e] = perm[g.lo + e];
+  __syncthreads();
+  constexpr int kStep = kSegThreads / 16;
+  auto at = [&](int64_t r) -> int64_t { return point[r]; };
+  double gm[Q], mean[Q] = {}, v[Q] = {}, acc[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) gm[q] = tc + 16 * q < d ? gmean[tc + 16 * q] : 0.0;
+  tree_sweep<Q, false>(x, d, t >> 4, len, kStep, tc, at, gm, mean, v, acc);
+  tree_gather<Q, W>(acc, d, tc, red, mean_s);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int k = tc + 16 * q;
+    mean[q] = k < d ? mean_s[k] / (double)len : 0.0;
+    v[q] = k < d ? tree_start(k) : 0.0;
+  }
+  for (int it = 0; it < kTreePowerIters; ++it) {
+    tree_sweep<Q, true>(x, d, t >> 4, len, kStep, tc, at, gm, mean, v, acc);
+    tree_gather<Q, W>(acc, d, tc, red, v_s);
+    if (t < 64) {
+      const double sc = tree_scale(v_s, d);
+      if (t == 0) scale_s = sc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int k = tc + 16 * q;
+      v[q] = k < d ? v_s[k] * scale_s : 0.0;
+    }
+    __syncthreads();
+  }
+  // projections; padding sorts last
+  int np2 = 2 * T;
+  while (np2 < len) np2 <<= 1;
+  tree_rows<Q>(x, d, t >> 4, len, kStep, tc, at, [&](int64_t e, int64_t, float (&c)[Q]) {
+    double w = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) w = fma(((double)c[q] - gm[q]) - mean[q], v[q], w);
+    w = rot16_sum_d(w);
+    if (tc == 0) key[e] = ((uint64_t)orderable_f32((float)w) << 32) | (uint32_t)e;
+  });
+  for (int e = len + t; e < np2; e += kSegThreads) key[e] = ~0ull;
+  __syncthreads();
+  // bitonic sort, one compare-exchange per thread and pair
+  for (int k = 2; k <= np2; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int c = t; c < np2 / 2; c += kSegThreads) {
+        const int lo = 2 * c - (c & (j - 1)), hi = lo + j;
+        const uint64_t a = key[lo], b = key[hi];
+        if ((a > b) == ((lo & k) == 0)) {
+          key[lo] = b;
+          key[hi] = a;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  for (int e = t; e < len; e += kSegThreads) perm[g.lo + e] = point[(uint32_t)key[e]];
+}
+
+// Levels whose segments are longer: chunk c of segment s (workgroup s C + c).
+// POWER: the chunk's part of the next direction, else of the mean.
+template <int Q, bool POWER>
+__global__ __launch_bounds__(kTreeThreads) void k_tree_chunk(
+    const float *__restrict__ x, const double *__restrict__ gmean, int32_t d, int64_t n,
+    int32_t nb, int level, int32_t C, const int32_t *__restrict__ perm,
+    const double *__restrict__ segmean,
+    const double *__restrict__ segv, double *__restrict__ part) {
+  __shared__ double red[kTreeThreads / 64][kTreeRowD];
+  __shared__ double out[kTreeRowD];
+  const int t = threadIdx.x, tc = t & 15;
+  const int64_t s = blockIdx.x / C, c = blockIdx.x % C;
+  const TreeSeg g = tree_segment(s, level, nb, n);
+  const int64_t len = g.hi - g.lo;
+  if (len <= T) return;
+  const int64_t r0 = g.lo + len * c / C, r1 = g.lo + len * (c + 1) / C;
+  double gm[Q], mean[Q], v[Q], acc[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int k = tc + 16 * q;
+    gm[q] = k < d ? gmean[k] : 0.0;
+    mean[q] = POWER && k < d ? segmean[s * d + k] : 0.0;
+    v[q] = POWER && k < d ? segv[s * d + k] : 0.0;
+  }
+  auto at = [&](int64_t r) -> int64_t { return perm[r]; };
+  tree_sweep<Q, POWER>(x, d, r0 + (t >> 4), r1, kTreeThreads / 16, tc, at, gm, mean, v, acc);
+  tree_gather<Q, kTreeThreads / 64>(acc, d, tc, red, out);
+  if (t < d) part[(int64_t)blockIdx.x * d + t] = out[t];
+}
+
+// Per segment: the chunk sums to the mean (and the start direction), or to the
+// next direction, normalised. A wave sums one coordinate's chunks.
+template <bool POWER>
+__global__ __launch_bounds__(kTreeThreads) void k_tree_join(const double *__restrict__ part,
+                                                            int32_t d, int64_t n, int32_t nb,
+                                                            int level, int32_t C,
+                                                            double *__restrict__ segmean,
+                                                            double *__restrict__ segv) {
+  __shared__ double out[kTreeRowD];
+  __shared__ double scale_s;
+  const int t = threadIdx.x, w = t >> 6, l = t & 63;
+  const int64_t s = blockIdx.x;
+  const TreeSeg g = tree_segment(s, level, nb, n);
+  if (g.hi - g.lo <= T) return;
+  for (int k = w; k < d; k += kTreeThreads / 64) {
+    double sum = 0.0;
+    for (int c = l; c < C; c += 64) sum += part[(s * C + c) * d + k];
+    sum = wave_sum_d(sum);
+    if (l == 0) out[k] = sum;
+  }
+  __syncthreads();
+  if (POWER && t < 64) {
+    const double sc = tree_scale(out, d);
+    if (t == 0) scale_s = sc;
+  }
+  __syncthreads();
+  if (t >= d) return;
+  if (POWER) {
+    segv[s * d + t] = out[t] * scale_s;
+  } else {
+    segmean[s * d + t] = out[t] / (double)(g.hi - g.lo);
+    segv[s * d + t] = tree_start(t);
+  }
+}
+
+// Sort keys of a chunk's rows, as k_tree_keys.
+template <int Q>
+__global__ __launch_bounds__(kTreeThreads) void k_tree_rowkeys(
+    const float *__restrict__ x, const double *__restrict__ gmean, int32_t d, int64_t n,
+    int32_t nb, int level, int32_t C, const int32_t *__restrict__ perm,
+    const double *__restrict__ segmean,
+    const double *__restrict__ segv, uint64_t *__restrict__ keys, int32_t *__restrict__ vals) {
+  const int t = threadIdx.x, tc = t & 15;
+  const int64_t s = blockIdx.x / C, c = blockIdx.x % C;
+  const TreeSeg g = tree_segment(s, level, nb, n);
+  const int64_t len = g.hi - g.lo;
+  const int64_t r0 = g.lo + len * c / C, r1 = g.lo + len * (c + 1) / C;
+  const uint64_t seg = (uint64_t)s << 32;
+  double gm[Q], mean[Q], v[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int k = tc + 16 * q;
+    gm[q] = k < d ? gmean[k] : 0.0;
+    mean[q] = len > T && k < d ? segmean[s * d + k] : 0.0;
+    v[q] = len > T && k < d ? segv[s * d + k] : 0.0;
+  }
+  auto at = [&](int64_t r) -> int64_t { return perm[r]; };
+  tree_rows<Q>(x, d, r0 + (t >> 4), r1, kTreeThreads / 16, tc, at,
+               [&](int64_t r, int64_t i, float (&cc)[Q]) {
+                 double w = 0.0;
+#pragma unroll
+                 for (int q = 0; q < Q; ++q) w = fma(((double)cc[q] - gm[q]) - mean[q], v[q], w);
+                 w = rot16_sum_d(w);
+                 if (tc == 0) {
+                   keys[r] = seg | (len > T ? (uint64_t)orderable_f32((float)w)
+                                            : (uint64_t)(r - g.lo));
+                   vals[r] = (int32_t)i;
+                 }
+               });
+}
+
 // Keys of positions beyond n sort last.
 __global__ void k_tree_pad(int64_t n, int64_t npow2, uint64_t *__restrict__ keys,
                            int32_t *__restrict__ vals) {
@@ -1915,13 +2221,6 @@ __device__ __forceinline__ double swap16_add(double x, double y) {
   const auto hi = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
   return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
          __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double x) {
-  const int2 a = __builtin_bit_cast(int2, x);
-  return x + __builtin_bit_cast(
-                 double, make_int2(__builtin_amdgcn_mov_dpp(a.x, CTRL, 0xf, 0xf, true),
-                                   __builtin_amdgcn_mov_dpp(a.y, CTRL, 0xf, 0xf, true)));
 }
 template <int R>
 __device__ __forceinline__ double rows_sum_d(const double (&x)[R]) {
@@ -2433,24 +2732,62 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
     const int64_t blk = L.npow2 < kSortBlock ? L.npow2 : kSortBlock;
     int levels = 0;
     while ((1 << levels) < L.nb) ++levels;
+    // coordinates per lane of the row kernels (0: d too large for them)
+    const int Q = L.d <= 16 ? 1 : L.d <= 32 ? 2 : L.d <= 64 ? 4 : L.d <= kTreeRowD ? 8 : 0;
+    auto rows = [&](auto run) {
+      if (Q == 1)
+        run(std::integral_constant<int, 1>{});
+      else if (Q == 2)
+        run(std::integral_constant<int, 2>{});
+      else if (Q == 4)
+        run(std::integral_constant<int, 4>{});
+      else
+        run(std::integral_constant<int, 8>{});
+    };
     for (int lev = 0; lev < levels; ++lev) {
       const int32_t S = 1 << lev;
       int32_t C = kTreeTargetGroups / S;
       if (C > L.nb / S) C = L.nb / S;  // at least a tile of rows per chunk on average
       if (C < 1) C = 1;
       const dim3 chunks((unsigned)(S * C)), segs((unsigned)S), tb(kTreeThreads);
-      hipLaunchKernelGGL(k_tree_partial<0>, chunks, tb, 0, st, xcT, L.npad, L.d, L.n, L.nb, lev, C,
-                         perm, segmean, segv, wbuf, part);
-      hipLaunchKernelGGL(k_tree_reduce<0>, segs, tb, 0, st, part, L.d, L.n, L.nb, lev, C, segmean,
-                         segv);
-      for (int it = 0; it < kTreePowerIters; ++it) {
-        hipLaunchKernelGGL(k_tree_partial<1>, chunks, tb, 0, st, xcT, L.npad, L.d, L.n, L.nb, lev,
-                           C, perm, segmean, segv, wbuf, part);
-        hipLaunchKernelGGL(k_tree_reduce<1>, segs, tb, 0, st, part, L.d, L.n, L.nb, lev, C,
-                           segmean, segv);
+      // segments of at most kSegRows rows (the longest has ceil(nb / S) tiles)
+      if (Q && (L.nb + S - 1) / S <= kSegRows / T) {
+        rows([&](auto q) {
+          hipLaunchKernelGGL(k_tree_seg<decltype(q)::value>, segs, dim3(kSegThreads), 0, st, x,
+                             mean, L.d, L.n, L.nb, lev, perm);
+        });
+        continue;
       }
-      hipLaunchKernelGGL(k_tree_keys, chunks, tb, 0, st, xcT, L.npad, L.d, L.n, L.nb, lev, C, perm,
-                         segmean, segv, keys, vals);
+      if (Q) {
+        rows([&](auto q) {
+          constexpr int kq = decltype(q)::value;
+          hipLaunchKernelGGL((k_tree_chunk<kq, false>), chunks, tb, 0, st, x, mean, L.d, L.n, L.nb,
+                             lev, C, perm, segmean, segv, part);
+          hipLaunchKernelGGL(k_tree_join<false>, segs, tb, 0, st, part, L.d, L.n, L.nb, lev, C,
+                             segmean, segv);
+          for (int it = 0; it < kTreePowerIters; ++it) {
+            hipLaunchKernelGGL((k_tree_chunk<kq, true>), chunks, tb, 0, st, x, mean, L.d, L.n, L.nb,
+                               lev, C, perm, segmean, segv, part);
+            hipLaunchKernelGGL(k_tree_join<true>, segs, tb, 0, st, part, L.d, L.n, L.nb, lev, C,
+                               segmean, segv);
+          }
+          hipLaunchKernelGGL(k_tree_rowkeys<kq>, chunks, tb, 0, st, x, mean, L.d, L.n, L.nb, lev, C,
+                             perm, segmean, segv, keys, vals);
+        });
+      } else {
+        hipLaunchKernelGGL(k_tree_partial<0>, chunks, tb, 0, st, xcT, L.npad, L.d, L.n, L.nb, lev,
+                           C, perm, segmean, segv, wbuf, part);
+        hipLaunchKernelGGL(k_tree_reduce<0>, segs, tb, 0, st, part, L.d, L.n, L.nb, lev, C, segmean,
+                           segv);
+        for (int it = 0; it < kTreePowerIters; ++it) {
+          hipLaunchKernelGGL(k_tree_partial<1>, chunks, tb, 0, st, xcT, L.npad, L.d, L.n, L.nb, lev,
+                             C, perm, segmean, segv, wbuf, part);
+          hipLaunchKernelGGL(k_tree_reduce<1>, segs, tb, 0, st, part, L.d, L.n, L.nb, lev, C,
+                             segmean, segv);
+        }
+        hipLaunchKernelGGL(k_tree_keys, chunks, tb, 0, st, xcT, L.npad, L.d, L.n, L.nb, lev, C,
+                           perm, segmean, segv, keys, vals);
+      }
       if (L.npow2 > L.n)
         hipLaunchKernelGGL(k_tree_pad, dim3((unsigned)((L.npow2 - L.n + 255) / 256)), dim3(256),
                            0, st, L.n, L.npow2, keys, vals);
