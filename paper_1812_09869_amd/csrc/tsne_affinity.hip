@@ -151,6 +151,8 @@ __global__ __launch_bounds__(256) void k_dist_f64(const double *__restrict__ xcT
                                                   int32_t dpad, int32_t b,
                                                   float *__restrict__ dblock,
                                                   float4 *__restrict__ P, int32_t nb) {
+  b += blockIdx.z;  // row block of the group, its distances in the group's slot
+  dblock += (size_t)blockIdx.z * T * npad;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int xs = (int)((blockIdx.x + 2u * (unsigned)b) % gridDim.x);  // column strip
   const int J = xs >> 1, cl = 128 * (xs & 1) + 32 * w;
@@ -289,6 +291,8 @@ __global__ __launch_bounds__(256) void k_dist_f32(const float *__restrict__ xfT,
                                                   const float *__restrict__ norms, int64_t npad,
                                                   int32_t dpad, int32_t b,
                                                   float *__restrict__ dblock) {
+  b += blockIdx.z;
+  dblock += (size_t)blockIdx.z * T * npad;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int64_t col0 = (int64_t)blockIdx.x * 256 + w * 64;
   const int row0_loc = blockIdx.y * 64;
@@ -340,6 +344,8 @@ __global__ __launch_bounds__(256) void k_dist_lp(const H *__restrict__ xa,
                                                  const float *__restrict__ norms, int64_t npad,
                                                  int32_t kk, int32_t b, float *__restrict__ dblock,
                                                  const Hdr *h) {
+  b += blockIdx.z;
+  dblock += (size_t)blockIdx.z * T * npad;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int64_t col0 = (int64_t)blockIdx.x * 256 + w * 64;
   const int row0_loc = blockIdx.y * 64;
@@ -567,6 +573,8 @@ __global__ __launch_bounds__(256, 2) void k_dist_x3(const H *__restrict__ xs,
                                                  int32_t k32, int32_t bits, int32_t b,
                                                  float *__restrict__ dblock, const Hdr *h,
                                                  float4 *__restrict__ P, int32_t nb) {
+  b += blockIdx.z;
+  dblock += (size_t)blockIdx.z * T * npad;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   // column tile, rotated so that the diagonal one (the workgroups with the
   // most stores) is dispatched first
@@ -802,16 +810,206 @@ __global__ __launch_bounds__(kCalThreads) void k_calibrate(const float *__restri
   }
 }
 
+// Sums over the wave of R rows' values. R = 1: every lane ends with the total.
+// R = 4: lane l ends with the total of row l / 16; the first two levels
+// (distances 32 and 16) exchange whole rows between the halves with the
+// lane-swap instructions, each halving the rows a lane carries, and the last
+// four rotate inside the 16 lanes. The additions are those of wave_sum_d's
+// butterfly, in its order (operands swapped at most), so the totals are too.
+__device__ __forceinline__ double swap32_add(double x, double y) {
+  const int2 a = __builtin_bit_cast(int2, x), b = __builtin_bit_cast(int2, y);
+  const auto lo = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
+         __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+__device__ __forceinline__ double swap16_add(double x, double y) {
+  const int2 a = __builtin_bit_cast(int2, x), b = __builtin_bit_cast(int2, y);
+  const auto lo = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
+         __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
+}
+template <int R>
+__device__ __forceinline__ double rows_sum_d(const double (&x)[R]) {
+  static_assert(R == 1 || R == 4, "a row to 16 lanes, or one row");
+  double v;
+  if constexpr (R == 1) {
+    v = swap32_add(x[0], x[0]);
+    v = swap16_add(v, v);
+  } else {
+    // lower half rows 0, 1, upper half rows 2, 3; then one row to 16 lanes
+    v = swap16_add(swap32_add(x[0], x[2]), swap32_add(x[1], x[3]));
+  }
+  v = dpp_add<0x128>(v);
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x122>(v);
+  return dpp_add<0x121>(v);
+}
+
+// The search of a row kept in the registers of one wave. Lane l holds the state
+// of row l / 16 (R = 4) or of the one row (R = 1): the FP64 arithmetic of a step,
+// several times the exponentials of 16 points a lane, is done once for all rows
+// of the wave.
+struct RowSearch {
+  double S, H;
+  float a, m;
+  int it, done;
+  // Results of row i, by one lane. bad: a non-finite distance.
+  __device__ void store(const CalOut &out, int64_t i, int64_t n, bool bad, Hdr *h) const {
+    out.beta[i] = (double)a * kLn2;
+    out.S[i] = S;
+    out.H[i] = H;
+    out.m[i] = m;
+    out.a[i] = a;
+    out.r[i] = (float)(1.0 / (2.0 * (double)n * S));
+    out.evals[i] = done == 1 ? it : -it;
+    if (done != 1) flag_error(h, kErrNoConv);
+    if (bad || !isfinite(H) || !isfinite(S)) flag_error(h, kErrNonFinite);
+  }
+};
+
+// v: the distances of the wave's rows, VPT per lane, INFINITY where excluded
+// (shifted by the row minimum in place). ok: the lane's row exists.
+template <int VPT, int R>
+__device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, bool ok,
+                                                 double logu, int max_bisect, double tol_h) {
+  const int g = R == 4 ? (threadIdx.x & 63) >> 4 : 0;
+  RowSearch f{0.0, 0.0, 0.f, 0.f, 0, ok ? 0 : 1};
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    float mn = INFINITY;
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) mn = fminf(mn, v[r][q]);
+    mn = wave_min_f(mn);
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) v[r][q] = (v[r][q] == INFINITY) ? kBig : v[r][q] - mn;
+    if (r == g) f.m = mn;
+  }
+  // Start of the search: at beta = 0 the entropy is ln(n - 1), its slope is
+  // zero and its curvature -Var(d), so it falls to ln u near
+  // beta = sqrt(2 ln((n - 1) / u) / Var(d)); one pass without exponentials. (From
+  // beta = 1, partial problems of 1,000 points at perplexity 400 took 13 passes,
+  // most of them halvings; from here 4.)
+  double beta, lo = 0.0, hi = INFINITY;
+  {
+    double T1[R], T2[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float t1 = 0.f, t2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < VPT; ++q) {
+        const float x = v[r][q] < kBig ? v[r][q] : 0.f;  // 0 for an excluded entry
+        t1 += x;
+        t2 = fmaf(x, x, t2);
+      }
+      T1[r] = (double)t1;
+      T2[r] = (double)t2;
+    }
+    const double cnt = (double)(n - 1), mean = rows_sum_d<R>(T1) / cnt;
+    const double var = rows_sum_d<R>(T2) / cnt - mean * mean;
+    beta = sqrt(2.0 * (log(cnt) - logu) / var);
+    if (!(beta > 0.0) || !isfinite(beta)) beta = 1.0;
+  }
+  while (!__all(f.done)) {
+    // a row that has stopped goes along with its last beta, unused
+    if (!f.done) {
+      ++f.it;
+      f.a = fmaxf((float)(beta * kLog2e), 1e-30f);
+    }
+    double SS[R], TT[R], QQ[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f.a), 16 * r));
+      float s = 0.f, tt = 0.f, qq = 0.f;
+#pragma unroll
+      for (int q = 0; q < VPT; ++q) {
+        const float ex = __builtin_amdgcn_exp2f(-ar * v[r][q]);
+        const float ve = v[r][q] * ex;  // 0 for an excluded entry (ex = 0)
+        s += ex;
+        tt += ve;
+        qq = fmaf(v[r][q], ve, qq);
+      }
+      SS[r] = (double)s;
+      TT[r] = (double)tt;
+      QQ[r] = (double)qq;
+    }
+    const double ss = rows_sum_d<R>(SS), ts = rows_sum_d<R>(TT), qs = rows_sum_d<R>(QQ);
+    if (f.done) continue;
+    const double beff = (double)f.a * kLn2;
+    f.S = ss;
+    const double mean = ts / ss;
+    f.H = log(ss) + beff * mean;
+    if (fabs(f.H - logu) <= tol_h) {
+      f.done = 1;
+    } else if (isfinite(hi) && (hi - lo) <= hi * 0x1p-24) {
+      f.done = 1;
+    } else if (f.it >= max_bisect) {
+      f.done = 2;
+    } else {
+      // H falls with beta (dH/dbeta = -beta Var(d)): shrink the bracket,
+      // then take the Newton step if it lands inside it, else bisect
+      // (the bracket holds the FP64 iterates; H was taken at their FP32
+      // rounding beff, within 2^-24 of beta)
+      if (f.H > logu)
+        lo = beta;
+      else
+        hi = beta;
+      const double var = qs / ss - mean * mean;
+      const double nb = beta + (f.H - logu) / (beff * var);
+      if (var > 0.0 && nb > lo && nb < hi && isfinite(nb))
+        beta = nb;
+      else
+        beta = isinf(hi) ? 2.0 * beta : 0.5 * (lo + hi);
+    }
+  }
+  return f;
+}
+
+// Search for problems of at most kCalWaveN points: R rows to a wave, as in the
+// many-problem path, instead of a workgroup of 1,024 threads to a row, most of
+// whose time at two points a thread went into its barriers and wave sums. All
+// rows of the problem in one launch (their distances fit in one group), each
+// from its own start. n = 2,000: 19 us against 149 (two launches).
+constexpr int64_t kCalWaveN = 4096;
+constexpr int kCalWaves = 4;  // waves per workgroup
+template <int VPT, int R>
+__global__ __launch_bounds__(kCalWaves * 64) void k_calibrate_wave(
+    const float *__restrict__ dblock, int64_t n, int64_t npad, int32_t b, double logu,
+    int max_bisect, double tol_h, CalOut out, Hdr *h) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int64_t r0 = ((int64_t)blockIdx.x * kCalWaves + w) * R;  // row within the group
+  const int64_t i0 = (int64_t)b * T + r0;
+  if (i0 >= n) return;
+  float v[R][VPT];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = i0 + r;
+    const float *row = dblock + (r0 + r) * npad;
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) {
+      const int64_t j = (int64_t)q * 64 + l;
+      v[r][q] = (i < n && j < n && j != i) ? row[j] : INFINITY;
+    }
+  }
+  const int g = R == 4 ? l >> 4 : 0;
+  const RowSearch f = search_rows<VPT, R>(v, n, i0 + g < n, logu, max_bisect, tol_h);
+  if ((R == 4 ? (l & 15) : l) == 0 && i0 + g < n) f.store(out, i0 + g, n, false, h);
+}
+
 // ----------------------------------------------------------------------------
 // 2c. Copy the block's tiles (b, J >= b) into the P store in consumer order.
 // The diagonal tile holds both orders of each pair; both take the distance
 // of the upper element so that the stored P is exactly symmetric.
 // ----------------------------------------------------------------------------
-// Grid (nb - b, kStageSplit).
+// Grid (nb - b, kStageSplit, blocks), blocks b .. of one group.
 constexpr int kStageSplit = 4;
 __global__ __launch_bounds__(256) void k_stage(const float *__restrict__ dblock, int64_t npad,
                                                int32_t nb, int32_t b, float4 *__restrict__ P) {
+  b += blockIdx.z;
+  dblock += (size_t)blockIdx.z * T * npad;
   const int J = b + blockIdx.x;
+  if (J >= nb) return;
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
   const int tc = l & 15, tr = (l >> 4) + 4 * w;
   float4 *dst = P + (size_t)tile_start(b, nb) * TT4 + (size_t)blockIdx.x * TT4;
@@ -1378,11 +1576,13 @@ constexpr int kSortBlock = 4096;         // keys per workgroup in the LDS sortin
 
 // Given dissimilarities (any measure may enter, section "ptSNE: parallelized
 // t-SNE"): the squares of rows b*T .. b*T + T - 1 of the n x n matrix into the
-// distance block, in place of the contraction. Grid (npad / 256, T / 16):
+// distance block, in place of the contraction. Grid (npad / 256, T / 16, blocks):
 // workgroup (c, g) covers columns 256 c .. 256 c + 255 of rows 16 g .. 16 g + 15.
 __global__ __launch_bounds__(256) void k_dissim_block(const float *__restrict__ dis, int64_t n,
                                                       int64_t npad, int32_t b,
                                                       float *__restrict__ dblock, Hdr *h) {
+  b += blockIdx.z;  // row block of the group, its squares in the group's slot
+  dblock += (size_t)blockIdx.z * T * npad;
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   bool bad = false;
   for (int r = 16 * blockIdx.y; r < 16 * (blockIdx.y + 1); ++r) {
@@ -2202,40 +2402,6 @@ __global__ __launch_bounds__(256) void k_small_init(const SmallEntry *__restrict
   e.inv[i] = (int32_t)i;
 }
 
-// Sums over the wave of R rows' values. R = 1: the butterfly of wave_sum_d,
-// every lane with the total. R = 4: lane l ends with the total of row l / 16;
-// the first two levels (distances 32 and 16) exchange whole rows between the
-// halves with the lane-swap instructions, each halving the rows a lane carries,
-// and the last four rotate inside the 16 lanes. The additions are the
-// butterfly's, in its order (operands swapped at most), so the totals are too.
-__device__ __forceinline__ double swap32_add(double x, double y) {
-  const int2 a = __builtin_bit_cast(int2, x), b = __builtin_bit_cast(int2, y);
-  const auto lo = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
-  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
-         __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
-}
-__device__ __forceinline__ double swap16_add(double x, double y) {
-  const int2 a = __builtin_bit_cast(int2, x), b = __builtin_bit_cast(int2, y);
-  const auto lo = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
-  return __builtin_bit_cast(double, make_int2(lo[0], hi[0])) +
-         __builtin_bit_cast(double, make_int2(lo[1], hi[1]));
-}
-template <int R>
-__device__ __forceinline__ double rows_sum_d(const double (&x)[R]) {
-  if constexpr (R == 1) {
-    return wave_sum_d(x[0]);
-  } else {
-    // lower half rows 0, 1, upper half rows 2, 3; then one row to 16 lanes
-    double v = swap16_add(swap32_add(x[0], x[2]), swap32_add(x[1], x[3]));
-    v = dpp_add<0x128>(v);
-    v = dpp_add<0x124>(v);
-    v = dpp_add<0x122>(v);
-    return dpp_add<0x121>(v);
-  }
-}
-
 // R rows to a wave. What bounds a pass over 1,000 points is not its 16
 // exponentials a lane but the three wave sums, the logarithm and the divisions
 // in FP64, which every lane repeats for the one row; and in the distances one
@@ -2351,120 +2517,16 @@ __global__ __launch_bounds__(kSmallWaves * 64) void k_small_calibrate(
     }
   }
   if (i0 >= n) return;  // no barrier below this point
-  const double logu = log(e.perplexity);
-  // From here lane l holds the search of row i0 + g, g = l / 16 (R = 4), or of
-  // the one row (R = 1): the FP64 arithmetic of a step, several times the
-  // exponentials of 16 points a lane, is done once for all rows of the wave.
-  static_assert(R == 1 || R == 4, "a row to 16 lanes, or one row");
   const int g = R == 4 ? l >> 4 : 0;
-  float m = 0.f;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    float mn = INFINITY;
-#pragma unroll
-    for (int q = 0; q < VPT; ++q) mn = fminf(mn, v[r][q]);
-    mn = wave_min_f(mn);
-#pragma unroll
-    for (int q = 0; q < VPT; ++q) v[r][q] = (v[r][q] == INFINITY) ? kBig : v[r][q] - mn;
-    if (r == g) m = mn;
-  }
-  // Start of the search: at beta = 0 the entropy is ln(n - 1), its slope is
-  // zero and its curvature -Var(d), so it falls to ln u near
-  // beta = sqrt(2 ln((n - 1) / u) / Var(d)); one pass without exponentials. (From
-  // beta = 1, partial problems of 1,000 points at perplexity 400 took 13 passes,
-  // most of them halvings; from here 4.)
-  double beta, lo = 0.0, hi = INFINITY, S = 0.0, H = 0.0;
-  {
-    double T1[R], T2[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      float t1 = 0.f, t2 = 0.f;
-#pragma unroll
-      for (int q = 0; q < VPT; ++q) {
-        const float x = v[r][q] < kBig ? v[r][q] : 0.f;  // 0 for an excluded entry
-        t1 += x;
-        t2 = fmaf(x, x, t2);
-      }
-      T1[r] = (double)t1;
-      T2[r] = (double)t2;
-    }
-    const double cnt = (double)(n - 1), mean = rows_sum_d<R>(T1) / cnt;
-    const double var = rows_sum_d<R>(T2) / cnt - mean * mean;
-    beta = sqrt(2.0 * (log(cnt) - logu) / var);
-    if (!(beta > 0.0) || !isfinite(beta)) beta = 1.0;
-  }
-  float a = 0.f;
-  int it = 0, done = i0 + g < n ? 0 : 1;  // rows past the end have no search
-  while (!__all(done)) {
-    // a row that has stopped goes along with its last beta, unused
-    if (!done) {
-      ++it;
-      a = fmaxf((float)(beta * kLog2e), 1e-30f);
-    }
-    double SS[R], TT[R], QQ[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 16 * r));
-      float s = 0.f, tt = 0.f, qq = 0.f;
-#pragma unroll
-      for (int q = 0; q < VPT; ++q) {
-        const float ex = __builtin_amdgcn_exp2f(-ar * v[r][q]);
-        const float ve = v[r][q] * ex;  // 0 for an excluded entry (ex = 0)
-        s += ex;
-        tt += ve;
-        qq = fmaf(v[r][q], ve, qq);
-      }
-      SS[r] = (double)s;
-      TT[r] = (double)tt;
-      QQ[r] = (double)qq;
-    }
-    const double ss = rows_sum_d<R>(SS), ts = rows_sum_d<R>(TT), qs = rows_sum_d<R>(QQ);
-    if (done) continue;
-    const double beff = (double)a * kLn2;
-    S = ss;
-    const double mean = ts / ss;
-    H = log(ss) + beff * mean;
-    if (fabs(H - logu) <= tol_h) {
-      done = 1;
-    } else if (isfinite(hi) && (hi - lo) <= hi * 0x1p-24) {
-      done = 1;
-    } else if (it >= max_bisect) {
-      done = 2;
-    } else {
-      // H falls with beta (dH/dbeta = -beta Var(d)): shrink the bracket,
-      // then take the Newton step if it lands inside it, else bisect
-      // (the bracket holds the FP64 iterates; H was taken at their FP32
-      // rounding beff, within 2^-24 of beta)
-      if (H > logu)
-        lo = beta;
-      else
-        hi = beta;
-      const double var = qs / ss - mean * mean;
-      const double nb = beta + (H - logu) / (beff * var);
-      if (var > 0.0 && nb > lo && nb < hi && isfinite(nb))
-        beta = nb;
-      else
-        beta = isinf(hi) ? 2.0 * beta : 0.5 * (lo + hi);
-    }
-  }
+  const RowSearch f = search_rows<VPT, R>(v, n, i0 + g < n, log(e.perplexity), max_bisect, tol_h);
   bool any_bad = false;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const bool ab = __any(bad[r]);
     if (r == g) any_bad = ab;
   }
-  const int64_t i = i0 + g;
-  if ((R == 4 ? (l & 15) : l) == 0 && i < n) {
-    e.beta[i] = (double)a * kLn2;
-    e.S[i] = S;
-    e.H[i] = H;
-    e.m[i] = m;
-    e.a[i] = a;
-    e.r[i] = (float)(1.0 / (2.0 * (double)n * S));
-    e.evals[i] = done == 1 ? it : -it;
-    if (done != 1) flag_error(e.h, kErrNoConv);
-    if (any_bad || !isfinite(H) || !isfinite(S)) flag_error(e.h, kErrNonFinite);
-  }
+  if ((R == 4 ? (l & 15) : l) == 0 && i0 + g < n)
+    f.store(CalOut{e.beta, e.S, e.H, e.m, e.a, e.r, e.evals}, i0 + g, n, any_bad, e.h);
 }
 
 __global__ __launch_bounds__(256) void k_small_pack(const SmallEntry *__restrict__ tab,
@@ -2548,17 +2610,17 @@ __global__ void k_set_ready(Hdr *h, int32_t ready) {
 // Host-side sequencing
 // ----------------------------------------------------------------------------
 
-// Distances of row block b against all columns into dblock (its slot of the
-// group scratch), in the workspace's distance mode. xc, nrm: the centred X and its norms for the
+// Distances of row blocks b .. b + blocks - 1 against all columns into dblock
+// (the group scratch), in the workspace's distance mode, one launch. xc, nrm: the centred X and its norms for the
 // FP64 mode (the reduced modes read their prepared operands).
 // P: the packed buffer, for the modes whose distance kernel stages the block
 // row's tiles itself (FP64 and the x3 modes), else nullptr. Returns whether
 // it did.
-static bool launch_dist(const Layout &L, void *ws, int b, const double *xc, const double *nrm,
-                        float *dblock, float4 *P, hipStream_t st) {
+static bool launch_dist(const Layout &L, void *ws, int b, int blocks, const double *xc,
+                        const double *nrm, float *dblock, float4 *P, hipStream_t st) {
   const Hdr *h = at<const Hdr>(ws, L.hdr);
   const float *norms32 = at<const float>(ws, L.norms32);
-  const dim3 dgrid((unsigned)(L.npad / 256), T / 64);
+  const dim3 dgrid((unsigned)(L.npad / 256), T / 64, (unsigned)blocks);
   switch (L.mode) {
     case TSNE_DIST_FP32:
       hipLaunchKernelGGL(k_dist_f32, dgrid, dim3(256), 0, st, at<const float>(ws, L.xfT), norms32,
@@ -2585,8 +2647,9 @@ static bool launch_dist(const Layout &L, void *ws, int b, const double *xc, cons
                          L.kk / 4, x3_bits(L.kk / 4, false), b, dblock, h, P, L.nb);
       return P != nullptr;
     default:
-      hipLaunchKernelGGL(k_dist_f64, dim3((unsigned)(L.npad / (64 * kDistCT)), T / 64), dim3(256),
-                         0, st, xc, nrm, L.npad, L.dpad, b, dblock, P, L.nb);
+      hipLaunchKernelGGL(k_dist_f64,
+                         dim3((unsigned)(L.npad / (64 * kDistCT)), T / 64, (unsigned)blocks),
+                         dim3(256), 0, st, xc, nrm, L.npad, L.dpad, b, dblock, P, L.nb);
       return P != nullptr;
   }
   return false;
@@ -2653,20 +2716,42 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
     }
   };
   // Row blocks are handled in groups of L.cal_group: block b's distances go
-  // to slot b - b0 of the scratch (b0 the group's first block).
-  auto slot = [&](int b) { return dblock + (size_t)(b % L.cal_group) * T * L.npad; };
+  // to slot b - b0 of the scratch (b0 the group's first block). One launch of
+  // each kernel per group.
   auto group_end = [&](int b0) { return b0 + L.cal_group < L.nb ? b0 + L.cal_group : L.nb; };
-  // Distances of row block b (into its slot), all columns.
-  // Whether the distance kernel staged the block row's tiles itself.
+  // Distances of a group's row blocks (into their slots), all columns.
+  // Whether the distance kernel staged the block rows' tiles itself.
   bool staged = false;
-  auto dist = [&](int b, const double *xc, const double *nrm) {
-    staged = launch_dist(L, ws, b, xc, nrm, slot(b), (stats_only || implicit) ? nullptr : P, st);
+  auto dist = [&](int b0, const double *xc, const double *nrm) {
+    staged = launch_dist(L, ws, b0, group_end(b0) - b0, xc, nrm, dblock,
+                         (stats_only || implicit) ? nullptr : P, st);
   };
   // The search over every row of the group starting at block b.
   auto calibrate = [&](int b) {
     const int64_t left = L.n - (int64_t)b * T, span = (int64_t)L.cal_group * T;
     const int rows = (int)(left < span ? left : span);
     dim3 g(rows), blk(kCalThreads);
+    if (L.n <= kCalWaveN && !stats_only) {
+#define TSNE_CAL(V, R)                                                                          \
+  hipLaunchKernelGGL((k_calibrate_wave<V, R>),                                                  \
+                     dim3((unsigned)((rows + kCalWaves * R - 1) / (kCalWaves * R))),            \
+                     dim3(kCalWaves * 64), 0, st, dblock, L.n, L.npad, b, logu, max_bisect,     \
+                     tol_h, co, h)
+      // (rows to a wave as in small_rows: distances of four rows stay in
+      // registers up to 16 a lane)
+      if (L.n <= 256)
+        TSNE_CAL(4, 4);
+      else if (L.n <= 512)
+        TSNE_CAL(8, 4);
+      else if (L.n <= 1024)
+        TSNE_CAL(16, 4);
+      else if (L.n <= 2048)
+        TSNE_CAL(32, 1);
+      else
+        TSNE_CAL(64, 1);
+#undef TSNE_CAL
+      return;
+    }
     if (vpt_need <= 1)
       hipLaunchKernelGGL(k_calibrate<1>, g, blk, 0, st, dblock, L.n, L.npad, b, logu, max_bisect,
                          tol_h, co, h);
@@ -2692,6 +2777,10 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
       hipLaunchKernelGGL(k_calibrate<0>, g, blk, 0, st, dblock, L.n, L.npad, b, logu, max_bisect,
                          tol_h, co, h);
   };
+  auto stage = [&](int b0) {
+    hipLaunchKernelGGL(k_stage, dim3(L.nb - b0, kStageSplit, (unsigned)(group_end(b0) - b0)),
+                       dim3(256), 0, st, dblock, L.npad, L.nb, b0, P);
+  };
   auto pack = [&]() {
     hipLaunchKernelGGL(k_pack, dim3((unsigned)L.nt), dim3(256), 0, st, P, co.a, co.m, co.r, L.n,
                        L.nb, ppart, nz, at<int2>(ws, L.tmap));
@@ -2706,13 +2795,11 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
     // given dissimilarities: no coordinates, so no ordering tree; the squared
     // rows take the place of the contraction
     for (int b0 = 0; b0 < L.nb; b0 += L.cal_group) {
-      for (int b = b0; b < group_end(b0); ++b)
-        hipLaunchKernelGGL(k_dissim_block, dim3((unsigned)(L.npad / 256), T / 16), dim3(256), 0,
-                           st, dis, L.n, L.npad, b, slot(b), h);
+      hipLaunchKernelGGL(k_dissim_block,
+                         dim3((unsigned)(L.npad / 256), T / 16, (unsigned)(group_end(b0) - b0)),
+                         dim3(256), 0, st, dis, L.n, L.npad, b0, dblock, h);
       calibrate(b0);
-      for (int b = b0; b < group_end(b0); ++b)
-        hipLaunchKernelGGL(k_stage, dim3(L.nb - b, kStageSplit), dim3(256), 0, st, slot(b),
-                           L.npad, L.nb, b, P);
+      stage(b0);
     }
     pack();
     return hipGetLastError();
@@ -2812,12 +2899,9 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
   // Distances, calibration and staging block by block, then P.
   prep(xc);
   for (int b0 = 0; b0 < L.nb; b0 += L.cal_group) {
-    for (int b = b0; b < group_end(b0); ++b) dist(b, xc, nrm);
+    dist(b0, xc, nrm);
     calibrate(b0);
-    if (!stats_only && !implicit && !staged)
-      for (int b = b0; b < group_end(b0); ++b)
-        hipLaunchKernelGGL(k_stage, dim3(L.nb - b, kStageSplit), dim3(256), 0, st, slot(b),
-                           L.npad, L.nb, b, P);
+    if (!stats_only && !implicit && !staged) stage(b0);
   }
   if (implicit) {
     // every pass rebuilds P from the contraction operands in the internal

@@ -28,6 +28,7 @@ constexpr int T = 256;             // tile edge
 constexpr int TT4 = T * T / 4;     // float4 per tile
 constexpr int kThreads = 256;      // threads per tile workgroup
 constexpr int kCalGroup = 4;       // row blocks per launch of the per-row search
+constexpr int kCalWhole = 16;      // up to so many (4,096 points), all of them in one launch
 // Problems of at most kSplitNb row blocks (2,048 points) run the force pass in
 // units of a quarter tile (kUnits = 4 per tile, 64 rows x 256 columns each): a
 // whole tile is 256 pairs per thread, and a small problem has too few tiles to
