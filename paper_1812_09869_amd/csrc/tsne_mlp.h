@@ -11,9 +11,8 @@ namespace tsne {
 struct MlpLayout {
   int d_in = 0, H = 0;
   int64_t Bpad = 0;
-  size_t w1b = 0, w2b = 0, w2tb = 0, xb = 0, h1b = 0, h2 = 0, loss_part = 0;
-  size_t xbt = 0, yb = 0, h1 = 0, h1t = 0, dout = 0, dh2 = 0, dh2b = 0, dh2t = 0, dh1 = 0,
-         dh1t = 0, gw1 = 0, colpart = 0;
+  size_t w1b = 0, w2b = 0, w2tb = 0;
+  size_t xbt = 0, h1t = 0, dh2t = 0, dh1t = 0, sums = 0, loss_part = 0;  // training
   size_t total = 0;
 };
 

@@ -24,92 +24,6 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 constexpr int kK1 = 64;  // d_in rounded up to the MFMA K step (d_in <= 64)
 
 // ----------------------------------------------------------------------------
-// Generic C[M][N] = sum_k A[m][k] B[n][k] on v_mfma_f32_16x16x32_bf16 with a
-// fused epilogue. One wave computes a 64 x 64 block (4 x 4 MFMA tiles); lane l
-// supplies rows l%16 of A and B with k-slice 8(l/16) .. 8(l/16)+7 and receives
-// D[4(l/16) + r][l%16] in element r. M, N multiples of 64, K of 32.
-// ----------------------------------------------------------------------------
-struct Epi {
-  const float *bias;   // per column n, or null
-  int relu;            // max(v, 0)
-  const float *mask;   // keep v only where mask[m * ldm + n] > 0, or null
-  int ldm;
-  float *outF;         // FP32 result [m * ldf + n] for n < nvalid, or null
-  int ldf, nvalid;
-  __bf16 *outB;        // BF16 result [m * ldb + n], or null
-  int ldb;
-  __bf16 *outBT;       // BF16 transposed result [n * ldt + m], or null
-  int ldt;
-};
-
-// KW waves per workgroup split K evenly (K / KW a multiple of 32); their
-// 64 x 64 partial results meet in LDS and wave 0 adds them in wave order
-// (a fixed order) before the epilogue.
-template <int KW>
-__global__ __launch_bounds__(64 * KW) void k_gemm_bf16(const __bf16 *__restrict__ A, int lda,
-                                                       const __bf16 *__restrict__ Bm, int ldbm,
-                                                       int K, Epi e) {
-  __shared__ v4f red[KW > 1 ? KW - 1 : 1][16][64];
-  const int64_t m0 = (int64_t)blockIdx.x * 64;
-  const int n0 = blockIdx.y * 64;
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, li = l & 15, lk = l >> 4;
-  v4f acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[a][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-  const int kpw = K / KW;
-  for (int k0 = wv * kpw; k0 < (wv + 1) * kpw; k0 += 32) {
-    v8bf av[4], bv[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-      av[a] = *reinterpret_cast<const v8bf *>(A + (m0 + a * 16 + li) * lda + k0 + 8 * lk);
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      bv[c] = *reinterpret_cast<const v8bf *>(Bm + (int64_t)(n0 + c * 16 + li) * ldbm + k0 +
-                                              8 * lk);
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[a], bv[c], acc[a][c], 0, 0, 0);
-  }
-  if (KW > 1) {
-    if (wv > 0) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) red[wv - 1][4 * a + c][l] = acc[a][c];
-    }
-    __syncthreads();
-    if (wv > 0) return;
-    for (int w = 0; w < KW - 1; ++w)
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] += red[w][4 * a + c][l];
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t m = m0 + a * 16 + 4 * lk + r;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int n = n0 + c * 16 + li;
-        float v = acc[a][c][r];
-        if (e.bias) v += e.bias[n];
-        if (e.relu) v = fmaxf(v, 0.f);
-        if (e.mask && !(e.mask[m * e.ldm + n] > 0.f)) v = 0.f;
-        if (e.outF && n < e.nvalid) e.outF[m * e.ldf + n] = v;
-        if (e.outB) e.outB[m * e.ldb + n] = (__bf16)v;
-        if (e.outBT) e.outBT[(int64_t)n * e.ldt + m] = (__bf16)v;
-      }
-    }
-  }
-}
-
-// ----------------------------------------------------------------------------
 // Fused inference. A persistent workgroup of W waves keeps the weights in
 // registers and runs tiles of kInferRows rows through the whole network:
 //
@@ -354,139 +268,349 @@ __global__ void k_mlp_cast(const float *__restrict__ p, int d_in, int H, __bf16 
   }
 }
 
-// Standardised BF16 inputs for a batch (rows idx[b] of x, or rows row0 + b).
-__global__ void k_mlp_gather(const float *__restrict__ x, int d_in, const float *__restrict__ mean,
-                             const float *__restrict__ invstd, const int32_t *__restrict__ idx,
-                             int64_t row0, int64_t B, int64_t Bpad, const float *__restrict__ y,
-                             __bf16 *__restrict__ xb, __bf16 *__restrict__ xbt,
-                             float *__restrict__ yb) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;  // one (row, input) element
-  if (e >= Bpad * kK1) return;
-  const int64_t b = e / kK1;
-  const int k = (int)(e % kK1);
-  const bool ok = b < B;
-  const int64_t r = ok ? (idx ? (int64_t)idx[b] : row0 + b) : 0;
-  float v = 0.f;
-  if (ok && k < d_in) v = (x[r * d_in + k] - mean[k]) * invstd[k];
-  const __bf16 hv = (__bf16)v;
-  xb[e] = hv;
-  if (xbt) xbt[(int64_t)k * Bpad + b] = hv;
-  if (yb && k < 2) yb[2 * b + k] = ok ? y[2 * r + k] : 0.f;
-}
+// ----------------------------------------------------------------------------
+// Training: one kernel takes a tile of 16 rows of the batch forward and back,
+// one more forms every parameter gradient. As single layers a step was 13
+// launches of 3 to 22 us, each the latency of a few dependent loads on 64
+// workgroups or fewer, with the activations written and read between them and
+// their transposes stored two bytes at a time.
+//
+// k_mlp_rows: wave w owns hidden units [H/W w, H/W (w + 1)) of both layers in
+// both directions and loads its rows of W1 and W2 while the inputs arrive and those
+// of W2^T beside the first layer. All three products are formed transposed, so a lane holds four
+// consecutive hidden units of one row, and the layers' operands pass through LDS:
+//   H1^T = W1 X^T, H2^T = W2 H1^T, out = W3 H2 + b3 (FP32, partial sums of the
+//   waves in LDS), dout = (out - y) / B, dH2 = W3^T dout where H2 > 0,
+//   dH1^T = W2^T dH2^T where H1 > 0.
+// The contractions' K steps are summed in KP parts whose sums are added in
+// order. Out of a tile go the BF16 operands of the weight gradients as
+// [tile][unit][16 rows], whose 16-byte pieces are the next kernel's operands,
+// and the tile's FP32 sums over its 16 rows for db1, db2, dW3, db3 and the loss.
+//
+// k_mlp_wgrad: workgroups of eight waves, 32 x 32 blocks of dW2 = dH2^T H1 and
+// dW1 = dH1^T X with the batch split over the waves (their partial results meet
+// in LDS, added in wave order); the last ones add the tiles' sums, in FP64.
+//
+// What bounds them at B = 1,024, H = 256 is the chain of one tile (index, row,
+// two layers, output, two layers back: five barriers), 14.2 us with cold caches,
+// and 4.2 us for the weight gradients; a gradient took 136 us and takes 21
+// (B = 4,096: 223 and 28; 65,536: 2,369 and 271).
+// ----------------------------------------------------------------------------
+constexpr int kTrainRows = 16;
 
-// Output layer of a training batch and its backward pass: out = W3 h2 + b3
-// (FP32), dout = (out - y) / B_total, per-row loss 0.5 |out - y|^2 summed per
-// workgroup, dh2 = (W3^T dout) masked by h2 > 0 (FP32, BF16 and BF16
-// transposed). Sixteen threads per row, each covering H / 16 consecutive
-// hidden units; the two outputs are summed over the 16 lanes of a DPP row.
-__global__ __launch_bounds__(256) void k_mlp_head(
-    const float *__restrict__ h2, int H, const float *__restrict__ w3, const float *__restrict__ b3,
-    int64_t B, int64_t Bpad, const float *__restrict__ yb, double inv_batch,
-    float *__restrict__ dout, float *__restrict__ dh2, __bf16 *__restrict__ dh2b,
-    __bf16 *__restrict__ dh2t, double *__restrict__ loss_part) {
-  __shared__ double red[4];
-  const int t = threadIdx.x, p = t & 15;
-  const int64_t b = (int64_t)blockIdx.x * 16 + (t >> 4);  // < Bpad: the grid is Bpad / 16
-  const int per = H / 16, k0 = p * per;
-  const float *hr = h2 + b * H + k0;
-  float o0 = 0.f, o1 = 0.f;
-  for (int j = 0; j < per; ++j) {
-    const float h = hr[j];
-    o0 = fmaf(w3[k0 + j], h, o0);
-    o1 = fmaf(w3[H + k0 + j], h, o1);
-  }
-  o0 = row16_sum_f(o0) + b3[0];
-  o1 = row16_sum_f(o1) + b3[1];
-  float d0 = 0.f, d1 = 0.f;
-  double lsum = 0.0;
-  if (b < B) {
-    const float e0 = o0 - yb[2 * b], e1 = o1 - yb[2 * b + 1];
-    if (p == 0) lsum = 0.5 * ((double)e0 * e0 + (double)e1 * e1);
-    d0 = (float)(e0 * inv_batch);
-    d1 = (float)(e1 * inv_batch);
-  }
-  if (p == 0) {
-    dout[2 * b] = d0;
-    dout[2 * b + 1] = d1;
-  }
-  for (int j = 0; j < per; ++j) {
-    const int k = k0 + j;
-    float g = fmaf(d0, w3[k], d1 * w3[H + k]);
-    if (!(hr[j] > 0.f)) g = 0.f;
-    dh2[b * H + k] = g;
-    dh2b[b * H + k] = (__bf16)g;
-    dh2t[(int64_t)k * Bpad + b] = (__bf16)g;
-  }
+template <int KS, int KP, int TW>
+__device__ __forceinline__ void train_layer(const v8bf (&wt)[TW][KS], const __bf16 *row, int g,
+                                            v4f (&acc)[TW]) {
+  v8bf b[KS];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
-  if ((t & 63) == 0) red[t >> 6] = lsum;
-  __syncthreads();
-  if (t == 0) loss_part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
-// Column sums over the batch, out[n] = sum_b wgt(b) D[b][n] with wgt(b) = 1
-// or w[b * wstride]: kColChunks chunks of rows summed in parallel (four
-// independent accumulators per thread), then the chunks added in order.
-// Several independent sums share one launch (blockIdx.z picks the job).
-constexpr int kColChunks = 32;
-constexpr int kColJobs = 4;
-
-struct ColJob {
-  const float *D;
-  const float *w;
-  float *part;  // [kColChunks][N]
-  float *out;   // [N]
-  int ldd, wstride, N;
-};
-struct ColJobs {
-  ColJob j[kColJobs];
-};
-
-__global__ __launch_bounds__(256) void k_colsum_part(ColJobs jobs, int64_t B) {
-  const ColJob &jb = jobs.j[blockIdx.z];
-  const int n = blockIdx.x * 256 + threadIdx.x, ch = blockIdx.y;
-  if (!jb.D || n >= jb.N) return;
-  const int64_t b0 = B * ch / kColChunks, b1 = B * (ch + 1) / kColChunks;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  int64_t b = b0;
-  for (; b + 3 < b1; b += 4) {
-    const float d0 = jb.D[b * jb.ldd + n], d1 = jb.D[(b + 1) * jb.ldd + n];
-    const float d2 = jb.D[(b + 2) * jb.ldd + n], d3 = jb.D[(b + 3) * jb.ldd + n];
-    if (jb.w) {
-      s0 = fmaf(jb.w[b * jb.wstride], d0, s0);
-      s1 = fmaf(jb.w[(b + 1) * jb.wstride], d1, s1);
-      s2 = fmaf(jb.w[(b + 2) * jb.wstride], d2, s2);
-      s3 = fmaf(jb.w[(b + 3) * jb.wstride], d3, s3);
-    } else {
-      s0 += d0;
-      s1 += d1;
-      s2 += d2;
-      s3 += d3;
+  for (int st = 0; st < KS; ++st)
+    b[st] = *reinterpret_cast<const v8bf *>(row + 32 * st + 8 * g);
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+#pragma unroll
+    for (int p = 0; p < KP; ++p) {
+      v4f s = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int st = KS / KP * p; st < KS / KP * (p + 1); ++st)
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[i][st], b[st], s, 0, 0, 0);
+      acc[i] = p ? acc[i] + s : s;
     }
   }
-  for (; b < b1; ++b) {
-    const float d = jb.D[b * jb.ldd + n];
-    s0 = jb.w ? fmaf(jb.w[b * jb.wstride], d, s0) : s0 + d;
-  }
-  jb.part[(int64_t)ch * jb.N + n] = (s0 + s1) + (s2 + s3);
 }
 
-__global__ __launch_bounds__(256) void k_colsum_fin(ColJobs jobs) {
-  const ColJob &jb = jobs.j[blockIdx.z];
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (!jb.D || n >= jb.N) return;
-  float s = 0.f;
-  for (int ch = 0; ch < kColChunks; ++ch) s += jb.part[(int64_t)ch * jb.N + n];
-  jb.out[n] = s;
+// Partial sums of a tile: db1[H], db2[H], dW3[2][H], db3[2].
+__host__ __device__ inline int train_sums(int H) { return 4 * H + 2; }
+
+template <int H, int W>
+__global__ __launch_bounds__(64 * W, 1) void k_mlp_rows(
+    const float *__restrict__ x, const float *__restrict__ y, int d_in,
+    const float *__restrict__ mean, const float *__restrict__ invstd,
+    const int32_t *__restrict__ idx, int64_t B, int64_t Bpad, const __bf16 *__restrict__ w1b,
+    const float *__restrict__ b1, const __bf16 *__restrict__ w2b,
+    const __bf16 *__restrict__ w2tb, const float *__restrict__ b2, const float *__restrict__ w3,
+    const float *__restrict__ b3, double inv_batch, __bf16 *__restrict__ xbt,
+    __bf16 *__restrict__ h1t, __bf16 *__restrict__ dh2t, __bf16 *__restrict__ dh1t,
+    float *__restrict__ sums, double *__restrict__ loss_part) {
+  constexpr int HW = H / W, TW = HW / 16, KS = H / 32;
+  constexpr int KP = KS % 4 == 0 ? 4 : 2;
+  constexpr int HPitch = H + 8;
+  __shared__ __bf16 xs[kTrainRows][kXPitch];
+  __shared__ __bf16 hs[kTrainRows][HPitch];  // H1, then dH2
+  __shared__ float po[W][kTrainRows][2];
+  __shared__ v4f vec[4][H / 4];  // b1, b2 and the two rows of W3
+  const int t = threadIdx.x, l = t & 63, w = t >> 6;
+  const int c = l & 15, g = l >> 4;
+  const int h0 = w * HW;
+  for (int e = t; e < 4 * H; e += 64 * W) {
+    const int j = e % H;
+    const float *src = e < H ? b1 + j : e < 2 * H ? b2 + j : w3 + (e - 2 * H);
+    reinterpret_cast<float *>(vec)[e] = *src;
+  }
+  v8bf wa[TW][2], wb[TW][KS], wt[TW][KS];
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+      wa[i][st] =
+          *reinterpret_cast<const v8bf *>(w1b + (h0 + 16 * i + c) * kK1 + 32 * st + 8 * g);
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+      wb[i][st] =
+          *reinterpret_cast<const v8bf *>(w2b + (h0 + 16 * i + c) * H + 32 * st + 8 * g);
+  }
+  const float c0 = b3[0], c1 = b3[1];
+  const int64_t tile = blockIdx.x;
+  const int64_t row0 = tile * kTrainRows;
+  // standardised inputs, zero past the batch and past d_in
+  for (int e = t; e < kTrainRows * kK1; e += 64 * W) {
+    const int r = e / kK1, k = e % kK1;
+    const int64_t b = row0 + r;
+    float v = 0.f;
+    if (b < B && k < d_in) {
+      const int64_t i = idx ? (int64_t)idx[b] : b;
+      v = (x[i * d_in + k] - mean[k]) * invstd[k];
+    }
+    xs[r][k] = (__bf16)v;
+  }
+  const int64_t br = row0 + c;  // this lane's row
+  __bf16 *h1o = h1t + row0 * H, *dh2o = dh2t + row0 * H, *dh1o = dh1t + row0 * H;
+  const bool live = br < B;
+  float y0 = 0.f, y1 = 0.f;
+  if (live) {
+    const int64_t i = idx ? (int64_t)idx[br] : br;
+    y0 = y[2 * i];
+    y1 = y[2 * i + 1];
+  }
+  __syncthreads();
+  __bf16 *xt = xbt + row0 * kK1;
+  for (int e = t; e < kTrainRows * kK1; e += 64 * W) {
+    const int k = e / kTrainRows, r = e % kTrainRows;
+    xt[e] = xs[r][k];
+  }
+#pragma unroll
+  for (int i = 0; i < TW; ++i)
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+      wt[i][st] =
+          *reinterpret_cast<const v8bf *>(w2tb + (h0 + 16 * i + c) * H + 32 * st + 8 * g);
+  // first layer
+  v4f acc[TW];
+  train_layer<2, 2, TW>(wa, xs[c], g, acc);
+  uint32_t on1 = 0;  // units of this lane with H1 > 0
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    v4bf hv;
+    const v4f bias = vec[0][(h0 + 16 * i) / 4 + g];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = h0 + 16 * i + 4 * g + r;
+      const float h = fmaxf(acc[i][r] + bias[r], 0.f);
+      on1 |= h > 0.f ? 1u << (4 * i + r) : 0u;
+      hv[r] = (__bf16)h;
+      h1o[kTrainRows * j + c] = hv[r];
+    }
+    *reinterpret_cast<v4bf *>(&hs[c][h0 + 16 * i + 4 * g]) = hv;
+  }
+  __syncthreads();
+  // second layer and the output layer's share of this wave
+  train_layer<KS, KP, TW>(wb, hs[c], g, acc);
+  float h2[TW][4], s0 = 0.f, s1 = 0.f;
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    const int v = (h0 + 16 * i) / 4 + g;
+    const v4f bias = vec[1][v], u0 = vec[2][v], u1 = vec[3][v];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h2[i][r] = live ? fmaxf(acc[i][r] + bias[r], 0.f) : 0.f;
+      s0 = fmaf(u0[r], h2[i][r], s0);
+      s1 = fmaf(u1[r], h2[i][r], s1);
+    }
+  }
+  s0 = add_xor16(add_xor32(s0));
+  s1 = add_xor16(add_xor32(s1));
+  if (g == 0) {
+    po[w][c][0] = s0;
+    po[w][c][1] = s1;
+  }
+  __syncthreads();  // also: every wave is done with H1 in hs
+  float o0 = 0.f, o1 = 0.f;
+#pragma unroll
+  for (int q = 0; q < W; ++q) {
+    o0 += po[q][c][0];
+    o1 += po[q][c][1];
+  }
+  const float e0 = live ? o0 + c0 - y0 : 0.f, e1 = live ? o1 + c1 - y1 : 0.f;
+  const float d0 = (float)(e0 * inv_batch), d1 = (float)(e1 * inv_batch);
+  float *sp = sums + tile * train_sums(H);
+  if (w == 0) {
+    double ls = l < 16 ? 0.5 * ((double)e0 * e0 + (double)e1 * e1) : 0.0;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);
+    const float t0 = row16_sum_f(d0), t1 = row16_sum_f(d1);
+    if (l == 0) {
+      loss_part[tile] = ls;
+      sp[4 * H] = t0;
+      sp[4 * H + 1] = t1;
+    }
+  }
+  // dH2, and the sums over the 16 rows
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    v4bf dv;
+    const int v = (h0 + 16 * i) / 4 + g;
+    const v4f u0 = vec[2][v], u1 = vec[3][v];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = h0 + 16 * i + 4 * g + r;
+      float dh = fmaf(d0, u0[r], d1 * u1[r]);
+      if (!(h2[i][r] > 0.f)) dh = 0.f;
+      dv[r] = (__bf16)dh;
+      dh2o[kTrainRows * j + c] = dv[r];
+      const float sb = row16_sum_f(dh), sw0 = row16_sum_f(d0 * h2[i][r]),
+                  sw1 = row16_sum_f(d1 * h2[i][r]);
+      if (c == 0) {
+        sp[H + j] = sb;
+        sp[2 * H + j] = sw0;
+        sp[3 * H + j] = sw1;
+      }
+    }
+    *reinterpret_cast<v4bf *>(&hs[c][h0 + 16 * i + 4 * g]) = dv;
+  }
+  __syncthreads();
+  train_layer<KS, KP, TW>(wt, hs[c], g, acc);
+#pragma unroll
+  for (int i = 0; i < TW; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = h0 + 16 * i + 4 * g + r;
+      const float dh = (on1 >> (4 * i + r)) & 1u ? acc[i][r] : 0.f;
+      dh1o[kTrainRows * j + c] = (__bf16)dh;
+      const float sb = row16_sum_f(dh);
+      if (c == 0) sp[j] = sb;
+    }
 }
 
-__global__ void k_loss_reduce(const double *__restrict__ part, int nparts, double inv_batch,
-                              double *out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int q = 0; q < nparts; ++q) s += part[q];
-    *out = s * inv_batch;
+constexpr int kWgWaves = 8;
+
+// C block (bm, bn) of 32 x 32: C[m][n] = sum_b A[m][b] D[n][b], columns n < nvalid;
+// A and D hold ma and na units to a tile of 16 rows.
+__device__ __forceinline__ void wgrad_block(const __bf16 *__restrict__ A, int ma,
+                                            const __bf16 *__restrict__ D, int na, int64_t Bpad,
+                                            int bm, int bn, float *__restrict__ C, int ldc,
+                                            int nvalid, v4f (*red)[4][64]) {
+  const int t = threadIdx.x, l = t & 63, w = t >> 6, li = l & 15, lk = l >> 4;
+  const int steps = (int)(Bpad / 32), s0 = steps * w / kWgWaves, s1 = steps * (w + 1) / kWgWaves;
+  v4f acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) acc[a][c] = (v4f){0.f, 0.f, 0.f, 0.f};
+  // batch rows 32 st + 8 lk .. + 7: tile 2 st + lk / 2, half lk % 2
+  const __bf16 *ap = A + ((int64_t)(lk >> 1) * ma + 32 * bm + li) * kTrainRows + 8 * (lk & 1);
+  const __bf16 *dp = D + ((int64_t)(lk >> 1) * na + 32 * bn + li) * kTrainRows + 8 * (lk & 1);
+  const int64_t as = 2 * kTrainRows * (int64_t)ma, ds = 2 * kTrainRows * (int64_t)na;
+  int st = s0;
+  for (; st + 4 <= s1; st += 4) {  // four steps' loads in flight
+    v8bf av[4][2], dv[4][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        av[u][a] = *reinterpret_cast<const v8bf *>(ap + as * (st + u) + 16 * kTrainRows * a);
+        dv[u][a] = *reinterpret_cast<const v8bf *>(dp + ds * (st + u) + 16 * kTrainRows * a);
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          acc[a][c] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][a], dv[u][c], acc[a][c], 0, 0, 0);
   }
+  for (; st < s1; ++st) {
+    v8bf av[2], dv[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      av[a] = *reinterpret_cast<const v8bf *>(ap + as * st + 16 * kTrainRows * a);
+      dv[a] = *reinterpret_cast<const v8bf *>(dp + ds * st + 16 * kTrainRows * a);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[a], dv[c], acc[a][c], 0, 0, 0);
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) red[w][2 * a + c][l] = acc[a][c];
+  __syncthreads();
+  // thread (q, lane): the waves' results of one MFMA tile in wave order
+  if (t >= 256) return;
+  const int q = t >> 6;
+  v4f s = red[0][q][l];
+#pragma unroll
+  for (int v = 1; v < kWgWaves; ++v) s += red[v][q][l];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = 32 * bm + 16 * (q >> 1) + 4 * lk + r, n = 32 * bn + 16 * (q & 1) + li;
+    if (n < nvalid) C[(int64_t)m * ldc + n] = s[r];
+  }
+}
+
+__global__ __launch_bounds__(64 * kWgWaves) void k_mlp_wgrad(
+    const __bf16 *__restrict__ xbt, const __bf16 *__restrict__ h1t,
+    const __bf16 *__restrict__ dh2t, const __bf16 *__restrict__ dh1t, int64_t Bpad, int H,
+    int d_in, const float *__restrict__ sums, const double *__restrict__ loss_part,
+    double inv_batch, float *__restrict__ g_w1, float *__restrict__ g_b1,
+    float *__restrict__ g_w2, float *__restrict__ g_b2, float *__restrict__ g_w3,
+    float *__restrict__ g_b3, double *__restrict__ loss) {
+  __shared__ v4f red[kWgWaves][4][64];
+  const int hb = H / 32, n2 = hb * hb, n1 = hb * (kK1 / 32);
+  const int wg = blockIdx.x;
+  if (wg < n2) {
+    wgrad_block(dh2t, H, h1t, H, Bpad, wg / hb, wg % hb, g_w2, H, H, red);
+    return;
+  }
+  if (wg < n2 + n1) {
+    const int q = wg - n2;
+    wgrad_block(dh1t, H, xbt, kK1, Bpad, q / (kK1 / 32), q % (kK1 / 32), g_w1, d_in, d_in, red);
+    return;
+  }
+  // sums over the tiles: 64 values to a workgroup, one to a lane, the tiles split over the
+  // waves, whose sums are added in order; the value past the sums is the loss
+  const int64_t tiles = Bpad / kTrainRows;
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int ns = train_sums(H), e = (wg - n2 - n1) * 64 + l;
+  const int64_t q0 = tiles * w / kWgWaves, q1 = tiles * (w + 1) / kWgWaves;
+  double s = 0.0;
+  if (e < ns) {
+    int64_t q = q0;
+    for (; q + 8 <= q1; q += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = sums[(q + u) * ns + e];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += (double)v[u];
+    }
+    for (; q < q1; ++q) s += (double)sums[q * ns + e];
+  } else if (e == ns) {
+    for (int64_t q = q0; q < q1; ++q) s += loss_part[q];
+  }
+  double(*part)[64] = reinterpret_cast<double(*)[64]>(red);
+  part[w][l] = s;
+  __syncthreads();
+  if (w > 0 || e > ns) return;
+#pragma unroll
+  for (int v = 1; v < kWgWaves; ++v) s += part[v][l];
+  if (e == ns) {
+    *loss = s * inv_batch;
+    return;
+  }
+  float *dst = e < H ? g_b1 + e : e < 2 * H ? g_b2 + (e - H)
+                                 : e < 4 * H ? g_w3 + (e - 2 * H) : g_b3 + (e - 4 * H);
+  *dst = (float)s;
 }
 
 __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -522,51 +646,17 @@ MlpLayout make_mlp_layout(int d_in, int H, int64_t Bpad, bool train) {
   L.w1b = take(Hs * kK1 * 2);
   L.w2b = take(Hs * Hs * 2);
   L.w2tb = take(Hs * Hs * 2);
-  L.xb = take(B * kK1 * 2);
-  L.h1b = take(B * Hs * 2);
-  L.h2 = take(B * Hs * 4);
-  L.loss_part = take((B / 16 + 1) * 8);
+  // (a forward pass keeps its activations in the kernel, whatever the batch)
   if (train) {
     L.xbt = take(B * kK1 * 2);
-    L.yb = take(B * 2 * 4);
-    L.h1 = take(B * Hs * 4);
     L.h1t = take(B * Hs * 2);
-    L.dout = take(B * 2 * 4);
-    L.dh2 = take(B * Hs * 4);
-    L.dh2b = take(B * Hs * 2);
     L.dh2t = take(B * Hs * 2);
-    L.dh1 = take(B * Hs * 4);
     L.dh1t = take(B * Hs * 2);
-    L.gw1 = take(Hs * kK1 * 4);
-    L.colpart = take((size_t)kColChunks * (4 * Hs + 2) * 4);
+    L.sums = take(B / kTrainRows * train_sums(H) * 4);
+    L.loss_part = take(B / kTrainRows * 8);
   }
   L.total = o;
   return L;
-}
-
-static Epi epi() {
-  Epi e{};
-  e.nvalid = 1 << 30;
-  return e;
-}
-
-// C = A B^T on (M / 64) x (N / 64) workgroups, splitting K over as many waves
-// (8, 4, 2 or 1) as divide its 32-wide steps, so that short grids with long
-// K still have enough loads in flight.
-static void gemm(int64_t M, int N, const __bf16 *A, int lda, const __bf16 *Bm, int ldb, int K,
-                 const Epi &e, hipStream_t st) {
-  const dim3 grid((unsigned)(M / 64), (unsigned)(N / 64));
-  const int steps = K / 32;
-  const int64_t tiles = M / 64 * (N / 64);
-  const int want = tiles >= 256 ? 1 : (tiles >= 64 ? 4 : 8);
-  if (want >= 8 && steps % 8 == 0)
-    hipLaunchKernelGGL(k_gemm_bf16<8>, grid, dim3(512), 0, st, A, lda, Bm, ldb, K, e);
-  else if (want >= 4 && steps % 4 == 0)
-    hipLaunchKernelGGL(k_gemm_bf16<4>, grid, dim3(256), 0, st, A, lda, Bm, ldb, K, e);
-  else if (want >= 2 && steps % 2 == 0)
-    hipLaunchKernelGGL(k_gemm_bf16<2>, grid, dim3(128), 0, st, A, lda, Bm, ldb, K, e);
-  else
-    hipLaunchKernelGGL(k_gemm_bf16<1>, grid, dim3(64), 0, st, A, lda, Bm, ldb, K, e);
 }
 
 // Forward pass of rows [row0, row0 + B) (or idx[0..B)) of x into out.
@@ -654,77 +744,38 @@ hipError_t launch_mlp_gradient(const MlpLayout &L, const float *params, const fl
   const float *w3 = b2 + H, *b3 = w3 + 2 * H;
   float *g_w1 = grad, *g_b1 = g_w1 + (int64_t)H * d_in, *g_w2 = g_b1 + H,
         *g_b2 = g_w2 + (int64_t)H * H, *g_w3 = g_b2 + H, *g_b3 = g_w3 + 2 * H;
-  __bf16 *xb = at<__bf16>(ws, L.xb), *xbt = at<__bf16>(ws, L.xbt), *h1b = at<__bf16>(ws, L.h1b),
-         *h1t = at<__bf16>(ws, L.h1t), *dh2b = at<__bf16>(ws, L.dh2b),
+  __bf16 *xbt = at<__bf16>(ws, L.xbt), *h1t = at<__bf16>(ws, L.h1t),
          *dh2t = at<__bf16>(ws, L.dh2t), *dh1t = at<__bf16>(ws, L.dh1t);
-  float *yb = at<float>(ws, L.yb), *h1 = at<float>(ws, L.h1), *h2 = at<float>(ws, L.h2),
-        *dout = at<float>(ws, L.dout), *dh2 = at<float>(ws, L.dh2), *dh1 = at<float>(ws, L.dh1);
+  float *sums = at<float>(ws, L.sums);
   double *lp = at<double>(ws, L.loss_part);
+  const double inv = 1.0 / (double)B;
   hipError_t err = launch_mlp_cast(L, params, ws, st);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_mlp_gather, dim3((unsigned)(Bpad * kK1 / 256)), dim3(256), 0, st, x, d_in,
-                     mean, invstd, idx, 0, B, Bpad, y, xb, xbt, yb);
-  // forward
-  Epi e1 = epi();
-  e1.bias = b1;
-  e1.relu = 1;
-  e1.outF = h1;
-  e1.ldf = H;
-  e1.outB = h1b;
-  e1.ldb = H;
-  e1.outBT = h1t;
-  e1.ldt = (int)Bpad;
-  gemm(Bpad, H, xb, kK1, at<const __bf16>(ws, L.w1b), kK1, kK1, e1, st);
-  Epi e2 = epi();
-  e2.bias = b2;
-  e2.relu = 1;
-  e2.outF = h2;
-  e2.ldf = H;
-  gemm(Bpad, H, h1b, H, at<const __bf16>(ws, L.w2b), H, H, e2, st);
-  const unsigned hgrid = (unsigned)(Bpad / 16);
-  hipLaunchKernelGGL(k_mlp_head, dim3(hgrid), dim3(256), 0, st, h2, H, w3, b3, B, Bpad, yb,
-                     1.0 / (double)B, dout, dh2, dh2b, dh2t, lp);
-  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(64), 0, st, lp, (int)hgrid, 1.0 / (double)B,
-                     loss);
-  // output layer gradients and db2: dW3[c][k] = sum_b dout[b][c] h2[b][k],
-  // db3[c] = sum_b dout[b][c], db2 = colsum(dh2)
-  float *cpart = at<float>(ws, L.colpart);
-  const size_t cstride = (size_t)kColChunks * H;
-  ColJobs jh{};
-  jh.j[0] = ColJob{h2, dout, cpart, g_w3, H, 2, H};
-  jh.j[1] = ColJob{h2, dout + 1, cpart + cstride, g_w3 + H, H, 2, H};
-  jh.j[2] = ColJob{dh2, nullptr, cpart + 2 * cstride, g_b2, H, 0, H};
-  jh.j[3] = ColJob{dout, nullptr, cpart + 4 * cstride, g_b3, 2, 0, 2};
-  const unsigned cgx = (unsigned)((H + 255) / 256);
-  hipLaunchKernelGGL(k_colsum_part, dim3(cgx, kColChunks, 4), dim3(256), 0, st, jh, Bpad);
-  // second layer: dW2 = dh2^T h1, dh1 = (dh2 W2) masked by h1 > 0
-  Epi ew2 = epi();
-  ew2.outF = g_w2;
-  ew2.ldf = H;
-  gemm(H, H, dh2t, (int)Bpad, h1t, (int)Bpad, (int)Bpad, ew2, st);
-  Epi ed1 = epi();
-  ed1.mask = h1;
-  ed1.ldm = H;
-  ed1.outF = dh1;
-  ed1.ldf = H;
-  ed1.outBT = dh1t;
-  ed1.ldt = (int)Bpad;
-  gemm(Bpad, H, dh2b, H, at<const __bf16>(ws, L.w2tb), H, H, ed1, st);
-  // first layer: dW1 = dh1^T xh (columns beyond d_in dropped), db1 = colsum(dh1)
-  Epi ew1 = epi();
-  ew1.outF = g_w1;
-  ew1.ldf = d_in;
-  ew1.nvalid = d_in;
-  gemm(H, kK1, dh1t, (int)Bpad, xbt, (int)Bpad, (int)Bpad, ew1, st);
-  ColJobs j1{};
-  j1.j[0] = ColJob{dh1, nullptr, cpart + 3 * cstride, g_b1, H, 0, H};
-  hipLaunchKernelGGL(k_colsum_part, dim3(cgx, kColChunks, 1), dim3(256), 0, st, j1, Bpad);
-  ColJobs jf = jh;
-  jf.j[3] = j1.j[0];
-  ColJobs jb3{};
-  jb3.j[0] = jh.j[3];
-  hipLaunchKernelGGL(k_colsum_fin, dim3(cgx, 1, 4), dim3(256), 0, st, jf);
-  hipLaunchKernelGGL(k_colsum_fin, dim3(1, 1, 1), dim3(256), 0, st, jb3);
+  const int64_t tiles = Bpad / kTrainRows;
+  const dim3 grid((unsigned)tiles);
+#define TSNE_ROWS(HH, W)                                                                        \
+  hipLaunchKernelGGL((k_mlp_rows<HH, W>), grid, dim3(64 * W), 0, st, x, y, d_in, mean, invstd,  \
+                     idx, B, Bpad, at<const __bf16>(ws, L.w1b), b1, at<const __bf16>(ws, L.w2b), \
+                     at<const __bf16>(ws, L.w2tb), b2, w3, b3, inv, xbt, h1t, dh2t, dh1t, sums, \
+                     lp)
+  switch (H) {
+    case 64:
+      TSNE_ROWS(64, 4);
+      break;
+    case 128:
+      TSNE_ROWS(128, 8);
+      break;
+    case 192:
+      TSNE_ROWS(192, 12);
+      break;
+    default:
+      TSNE_ROWS(256, 16);
+  }
+#undef TSNE_ROWS
+  const int hb = H / 32;
+  const unsigned wgs = (unsigned)(hb * hb + hb * (kK1 / 32) + train_sums(H) / 64 + 1);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(wgs), dim3(64 * kWgWaves), 0, st, xbt, h1t, dh2t, dh1t, Bpad,
+                     H, d_in, sums, lp, inv, g_w1, g_b1, g_w2, g_b2, g_w3, g_b3, loss);
   return hipGetLastError();
 }
 
