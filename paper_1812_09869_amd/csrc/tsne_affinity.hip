@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "tsne_internal.h"
+#include "tsne_tile.h"
 
 namespace tsne {
 
@@ -22,7 +23,6 @@ constexpr double kLog2e = 1.4426950408889634074;
 constexpr double kLn2 = 0.69314718055994530942;
 constexpr float kBig = 3.0e38f;  // stands for an excluded entry (self pair)
 
-typedef double v4d __attribute__((ext_vector_type(4)));
 
 __device__ inline void flag_error(Hdr *h, uint32_t bit) { atomicOr(&h->err, bit); }
 
@@ -134,9 +134,6 @@ __global__ __launch_bounds__(256) void k_centre(const float *__restrict__ x, int
 // per SIMD); a workgroup of 4 waves covers 64 rows x 64 kDistCT columns.
 // ----------------------------------------------------------------------------
 constexpr int kDistCT = 2;  // 16-column MFMA tiles per wave (a wave covers 64 x 16 kDistCT)
-// the implicit tile kernel's width: two 16-column tiles per wave, so that a
-// lane's two columns are neighbours in the tile layout
-constexpr int kTileCT = 2;
 
 // With P given, the block row's tiles (J >= b) also go straight to their
 // place in the packed buffer, in the layout k_stage writes, as in k_dist_x3:
@@ -241,19 +238,6 @@ __global__ __launch_bounds__(256) void k_dist_f64(const double *__restrict__ xcT
 // 16x16x32 layout: lane l supplies A[l%16][8(l/16) .. 8(l/16)+7] and the
 // matching B column slice, and receives D[4(l/16) + r][l%16] in element r.
 // ----------------------------------------------------------------------------
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-__device__ inline float fp16_scale(const Hdr *h) {
-  // 2^(8 - ceil(log2 xmax)); 1 if xmax is 0
-  const float xm = h->xmax;
-  if (!(xm > 0.f)) return 1.f;
-  int e;
-  frexpf(xm, &e);  // xm = f 2^e, f in [0.5, 1)
-  return ldexpf(1.f, 8 - e);
-}
-
 __global__ __launch_bounds__(256) void k_prep_f32(const double *__restrict__ xcT, int64_t npad,
                                                   int32_t dpad, float *__restrict__ xfT,
                                                   float *__restrict__ norms32) {
@@ -432,23 +416,6 @@ __global__ __launch_bounds__(256) void k_dist_lp(const H *__restrict__ xa,
 // 32 values in a row ([point][k / 32][slice][32]), so that the four
 // fragments a lane loads for one MFMA step sit in one 256-byte segment.
 // ----------------------------------------------------------------------------
-__host__ __device__ inline int x3_bits(int32_t k32, bool bf16) {
-  int lk = 0;
-  while ((1 << lk) < k32) ++lk;
-  const int b = (24 - lk) / 2;
-  const int bmax = bf16 ? 8 : 10;
-  return b < bmax ? b : bmax;
-}
-
-// E with max |x| < 2^E (0 for an all-zero input)
-__device__ inline int x3_exp(const Hdr *h) {
-  const float xm = h->xmax;
-  if (!(xm > 0.f)) return 0;
-  int e;
-  frexpf(xm, &e);
-  return e;
-}
-
 template <typename H>
 __global__ __launch_bounds__(256) void k_prep_x3(const double *__restrict__ xcT, int64_t npad,
                                                  int32_t d, int32_t k32, int32_t b,
@@ -477,88 +444,6 @@ __global__ __launch_bounds__(256) void k_prep_x3(const double *__restrict__ xcT,
   }
   const float hi = (float)nrm;
   nhl[i] = make_float2(hi, (float)(nrm - (double)hi));
-}
-
-template <typename H, typename V8>
-__device__ __forceinline__ v4f mfma16x32(V8 a, V8 b, v4f c) {
-  if constexpr (__is_same(H, __bf16))
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-
-// The two sums A0 and R of a 64 x 64 block (4 x 4 MFMA tiles): rows ra .. ra+63
-// against columns cb .. cb+63. Stored and recomputed P call this same routine,
-// so their sums agree bit for bit.
-template <typename H, typename V8>
-__device__ __forceinline__ void x3_contract(const H *__restrict__ xs, int32_t k32, int64_t ra,
-                                            int64_t cb, int li, int lk, v4f (&A0)[4][4],
-                                            v4f (&R)[4][4]) {
-  const int64_t kk = 4 * (int64_t)k32;
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      A0[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-      R[t][c] = A0[t][c];
-    }
-  for (int k0 = 0; k0 < k32; k0 += 32) {
-    const int64_t off = (int64_t)(k0 >> 5) * 128 + 8 * lk;
-    V8 a[4][4];  // [slice][row tile]: h1, h2, 2^-b h2, 2^-b h3
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        a[q][t] = *reinterpret_cast<const V8 *>(xs + (ra + 16 * t + li) * kk + off + 32 * q);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      V8 bv[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        bv[q] = *reinterpret_cast<const V8 *>(xs + (cb + 16 * c + li) * kk + off + 32 * q);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) A0[t][c] = mfma16x32<H, V8>(a[0][t], bv[0], A0[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[0][t], bv[1], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[1][t], bv[0], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[0][t], bv[3], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[1][t], bv[2], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[3][t], bv[0], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[2][t], bv[3], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[3][t], bv[2], R[t][c]);
-    }
-  }
-}
-
-// 2 sigma^2 and 2 sigma^2 2^-b
-struct X3Scale {
-  float s0, s1;
-};
-__device__ inline X3Scale x3_scale(const Hdr *h, int b) {
-  const int e = 2 * (x3_exp(h) - b) + 1;
-  return X3Scale{ldexpf(1.f, e), ldexpf(1.f, e - b)};
-}
-
-// d = n_i + n_j - 2 x.y from (hi, lo) norms and the two sums. The sum of the
-// hi parts is taken with TwoSum (its rounding error e is kept); the leading
-// difference t = s - 2 sigma^2 A0 needs no correction: the product is exact,
-// and where the operands cancel (2 sigma^2 A0 >= s / 2, i.e. d below about
-// s / 2) the subtraction is exact by Sterbenz's lemma, while elsewhere its
-// rounding is below one FP32 ulp of d itself.
-__device__ __forceinline__ float x3_combine(float2 ni, float2 nj, float a0, float r,
-                                            const X3Scale &sc) {
-  const float s = __fadd_rn(ni.x, nj.x);
-  const float bs = __fsub_rn(s, ni.x);
-  const float e = __fadd_rn(__fsub_rn(ni.x, __fsub_rn(s, bs)), __fsub_rn(nj.x, bs));
-  const float t = __fsub_rn(s, __fmul_rn(sc.s0, a0));  // a0: an integer below 2^24
-  const float low = __fsub_rn(__fadd_rn(e, __fadd_rn(ni.y, nj.y)), __fmul_rn(sc.s1, r));
-  return fmaxf(__fadd_rn(t, low), 0.f);
 }
 
 // Distance block of the x3 modes: a workgroup covers 64 rows x 256 columns,
@@ -1040,373 +925,27 @@ __global__ __launch_bounds__(256) void k_stage(const float *__restrict__ dblock,
 }
 
 // ----------------------------------------------------------------------------
-// 2d. Implicit P: distances straight into the tile buffer. One launch covers
-// the tiles tile0 .. tile0 + gridDim.x - 1 (whole block rows) and writes each
-// tile's distances in the layout k_stage produces (float4 s * 256 + t of a
-// tile holds rows tr + 16 (s / 4), columns tc + 64 (s % 4) + 16 e), so the
-// pack and force kernels read them as before. The contraction of an element
-// is the one the per-block-row kernels form for it (same operands, same
-// MFMA sequence); a diagonal tile takes the upper element for both orders of
-// a pair, as k_stage does, so P stays bitwise symmetric and bitwise that of
-// the stored path. skip: the zero tiles are known and are left alone.
+// 2d. Implicit P: the distances (or with PACK the P) of the tiles tile0 .. tile0 +
+// gridDim.x - 1 (whole block rows) straight into the tile buffer, strips over
+// blockIdx.y. skip: the zero tiles are known and are left alone.
 // ----------------------------------------------------------------------------
-// p_ij of Eq. 3 from the distance and both rows' statistics (a = beta
-// log2(e), m = row minimum, r = 1 / (2 n S)). No contraction into an FMA, so
-// that the two orders of a pair give bitwise equal sums.
-__device__ __forceinline__ float pair_p(float d, float ai, float mi, float ri, float aj, float mj,
-                                        float rj) {
-#pragma clang fp contract(off)
-  const float pi = __builtin_amdgcn_exp2f(-ai * (d - mi)) * ri;
-  const float pj = __builtin_amdgcn_exp2f(-aj * (d - mj)) * rj;
-  return pi + pj;
-}
-
-__device__ __forceinline__ int64_t tile_pos(int il, int jl) {
-  const int tr = il & 15, k = il >> 4, tc = jl & 15, mq = jl >> 6, e = (jl >> 4) & 3;
-  const int t = 64 * (tr >> 2) + 16 * (tr & 3) + tc;
-  return ((int64_t)(4 * k + mq) * 256 + t) * 4 + e;
-}
-
-__device__ __forceinline__ void put_d(float *__restrict__ tp, bool diag, int il, int jl,
-                                      float v) {
-  if (!diag) {
-    tp[tile_pos(il, jl)] = v;
-  } else if (il < jl) {
-    tp[tile_pos(il, jl)] = v;
-    tp[tile_pos(jl, il)] = v;
-  } else if (il == jl) {
-    tp[tile_pos(il, il)] = v;
-  }
-}
-
-// Statistics (a, m, r) of one point for the PACK epilogue; ok = false for a
-// padding point (its pairs are stored as 0).
-struct PtStat {
-  float a, m, r;
-  bool ok;
-};
-
-template <bool PACK>
-__device__ __forceinline__ PtStat pt_stat(int64_t g, int64_t n, const float *__restrict__ a,
-                                          const float *__restrict__ m,
-                                          const float *__restrict__ r) {
-  PtStat p{0.f, 0.f, 0.f, false};
-  if (PACK && g < n) p = PtStat{a[g], m[g], r[g], true};
-  return p;
-}
-
-// The stored value of one element: the distance, or with PACK its p_ij (the
-// packed value k_pack would write: zero on the diagonal, for padding points
-// and below FP32's normal range).
-template <bool PACK>
-__device__ __forceinline__ float tile_value(float d, bool diag, int il, int jl, const PtStat &si,
-                                            const PtStat &sj) {
-  if (!PACK) return d;
-  if ((diag && il == jl) || !si.ok || !sj.ok) return 0.f;
-  const float v = pair_p(d, si.a, si.m, si.r, sj.a, sj.m, sj.r);
-  return v < FLT_MIN ? 0.f : v;
-}
-
-// Common start: header check (a workspace prepared for another n, d or mode
-// is flagged and left alone), zero-tile skip, tile coordinates. Returns false
-// if the workgroup has nothing to do.
-__device__ __forceinline__ bool tdist_begin(const Hdr *guard, int64_t gn, int32_t gkey,
-                                            const uint8_t *__restrict__ nz, bool skip,
-                                            int64_t tile, int32_t nb, int &I, int &J) {
-  if (!implicit_ready(guard, gn, gkey)) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
-      flag_error(const_cast<Hdr *>(guard), kErrState);
-    return false;
-  }
-  if (skip && !nz[tile]) return false;
-  tile_coords(tile, nb, I, J);
-  return true;
-}
-
-// FP64 mode: a workgroup covers 64 rows x 128 columns of a tile (grid y: 4
-// row groups x 2 column groups), as k_dist_f64. a, m, r: the row statistics
-// (read with PACK only).
-template <bool PACK>
-__global__ __launch_bounds__(256) void k_tdist_f64(const double *__restrict__ xcT,
-                                                   const double *__restrict__ norms, int64_t npad,
-                                                   int32_t dpad, int32_t nb, int64_t tile0,
-                                                   int64_t tile_base, float *__restrict__ Pb,
-                                                   const Hdr *guard, int64_t gn, int32_t gkey,
-                                                   const uint8_t *__restrict__ nz, bool skip,
-                                                   const float *__restrict__ ra,
-                                                   const float *__restrict__ rm,
-                                                   const float *__restrict__ rr) {
-  const int64_t tile = tile0 + blockIdx.x;
-  int I, J;
-  if (!tdist_begin(guard, gn, gkey, nz, skip, tile, nb, I, J)) return;
-  const int ry = blockIdx.y & 3, cx = blockIdx.y >> 2;
-  const bool diag = (I == J);
-  if (diag && 64 * ry >= 64 * kTileCT * (cx + 1)) return;  // wholly below the diagonal
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int cl0 = 64 * kTileCT * cx + w * (16 * kTileCT);  // first column in the tile
-  const int64_t col0 = (int64_t)J * T + cl0;
-  const int row0_loc = 64 * ry;
-  const int64_t row0 = (int64_t)I * T + row0_loc;
-  const int li = l & 15, lk = l >> 4;
-  v4d acc[4][kTileCT];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < kTileCT; ++c) acc[a][c] = (v4d){0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < dpad; k0 += 4) {
-    const double *xk = xcT + (int64_t)(k0 + lk) * npad;
-    double av[4], bv[kTileCT];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) av[a] = xk[row0 + a * 16 + li];
-#pragma unroll
-    for (int c = 0; c < kTileCT; ++c) bv[c] = xk[col0 + c * 16 + li];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < kTileCT; ++c)
-        acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[c], acc[a][c], 0, 0, 0);
-  }
-  float *tp = Pb + (size_t)(tile - tile_base) * T * T;
-  PtStat sc[kTileCT];
-#pragma unroll
-  for (int c = 0; c < kTileCT; ++c)
-    sc[c] = pt_stat<PACK>((int64_t)J * T + cl0 + c * 16 + li, gn, ra, rm, rr);
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int il = row0_loc + a * 16 + lk + 4 * r;
-      const double ni = norms[(int64_t)I * T + il];
-      const PtStat si = pt_stat<PACK>((int64_t)I * T + il, gn, ra, rm, rr);
-      float v[kTileCT];
-#pragma unroll
-      for (int c = 0; c < kTileCT; ++c) {
-        const int jl = cl0 + c * 16 + li;
-        const double dd = ni + norms[(int64_t)J * T + jl] - 2.0 * acc[a][c][r];
-        v[c] = tile_value<PACK>((float)fmax(dd, 0.0), diag, il, jl, si, sc[c]);
-      }
-      // the lane's columns are consecutive elements (e, e + 1) of one float4
-      // slot of the tile layout: one 8-byte store off the diagonal
-      static_assert(kTileCT == 2, "two columns per lane");
-      if (!diag) {
-        *reinterpret_cast<float2 *>(tp + tile_pos(il, cl0 + li)) = make_float2(v[0], v[1]);
-      } else {
-#pragma unroll
-        for (int c = 0; c < kTileCT; ++c) put_d(tp, true, il, cl0 + c * 16 + li, v[c]);
-      }
-    }
-  }
-}
-
-// FP32 mode: a workgroup covers 64 rows x 256 columns (grid y: 4 row groups),
-// as k_dist_f32.
-template <bool PACK>
-__global__ __launch_bounds__(256) void k_tdist_f32(const float *__restrict__ xfT,
-                                                   const float *__restrict__ norms, int64_t npad,
-                                                   int32_t dpad, int32_t nb, int64_t tile0,
-                                                   int64_t tile_base, float *__restrict__ Pb,
-                                                   const Hdr *guard, int64_t gn, int32_t gkey,
-                                                   const uint8_t *__restrict__ nz, bool skip,
-                                                   const float *__restrict__ ra,
-                                                   const float *__restrict__ rm,
-                                                   const float *__restrict__ rr) {
-  const int64_t tile = tile0 + blockIdx.x;
-  int I, J;
-  if (!tdist_begin(guard, gn, gkey, nz, skip, tile, nb, I, J)) return;
-  const bool diag = (I == J);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int cl0 = w * 64;
-  const int64_t col0 = (int64_t)J * T + cl0;
-  const int row0_loc = blockIdx.y * 64;
-  const int64_t row0 = (int64_t)I * T + row0_loc;
-  const int li = l & 15, lk = l >> 4;
-  v4f acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[a][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < dpad; k0 += 4) {
-    const float *xk = xfT + (int64_t)(k0 + lk) * npad;
-    float av[4], bv[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) av[a] = xk[row0 + a * 16 + li];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) bv[c] = xk[col0 + c * 16 + li];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[c], acc[a][c], 0, 0, 0);
-  }
-  float *tp = Pb + (size_t)(tile - tile_base) * T * T;
-  PtStat sc[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-    sc[c] = pt_stat<PACK>((int64_t)J * T + cl0 + c * 16 + li, gn, ra, rm, rr);
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int il = row0_loc + a * 16 + 4 * lk + r;
-      const float ni = norms[(int64_t)I * T + il];
-      const PtStat si = pt_stat<PACK>((int64_t)I * T + il, gn, ra, rm, rr);
-      float v[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int jl = cl0 + c * 16 + li;
-        const float dd = (ni + norms[(int64_t)J * T + jl]) - 2.f * acc[a][c][r];
-        v[c] = tile_value<PACK>(fmaxf(dd, 0.f), diag, il, jl, si, sc[c]);
-      }
-      // the lane's four columns are the four elements of one float4 slot of
-      // the tile layout: one 16-byte store off the diagonal
-      if (!diag) {
-        *reinterpret_cast<float4 *>(tp + tile_pos(il, cl0 + li)) =
-            make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) put_d(tp, true, il, cl0 + c * 16 + li, v[c]);
-      }
-    }
-  }
-}
-
-// 16-bit modes: as k_dist_lp, a workgroup covers 64 rows x 256 columns.
-template <typename H, typename V8, bool SCALE, bool PACK>
-__global__ __launch_bounds__(256) void k_tdist_lp(const H *__restrict__ xa,
-                                                  const float *__restrict__ norms, int32_t kk,
-                                                  int32_t nb, int64_t tile0, int64_t tile_base,
-                                                  float *__restrict__ Pb, const Hdr *guard,
-                                                  int64_t gn, int32_t gkey,
-                                                  const uint8_t *__restrict__ nz, bool skip,
-                                                  const float *__restrict__ ra,
-                                                  const float *__restrict__ rm,
-                                                  const float *__restrict__ rr) {
-  const int64_t tile = tile0 + blockIdx.x;
-  int I, J;
-  if (!tdist_begin(guard, gn, gkey, nz, skip, tile, nb, I, J)) return;
-  const bool diag = (I == J);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int cl0 = w * 64;
-  const int64_t col0 = (int64_t)J * T + cl0;
-  const int row0_loc = blockIdx.y * 64;
-  const int64_t row0 = (int64_t)I * T + row0_loc;
-  const int li = l & 15, lk = l >> 4;
-  float inv_s2 = 1.f;
-  if (SCALE) {
-    const float s = fp16_scale(guard);
-    inv_s2 = 1.f / (s * s);
-  }
-  v4f acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[a][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < kk; k0 += 32) {
-    V8 av[4], bv[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-      av[a] = *reinterpret_cast<const V8 *>(xa + (row0 + a * 16 + li) * kk + k0 + 8 * lk);
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      bv[c] = *reinterpret_cast<const V8 *>(xa + (col0 + c * 16 + li) * kk + k0 + 8 * lk);
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if constexpr (sizeof(H) == 2 && __is_same(H, __bf16))
-          acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[a], bv[c], acc[a][c], 0, 0, 0);
-        else
-          acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[a], bv[c], acc[a][c], 0, 0, 0);
-      }
-  }
-  float *tp = Pb + (size_t)(tile - tile_base) * T * T;
-  PtStat sc[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-    sc[c] = pt_stat<PACK>((int64_t)J * T + cl0 + c * 16 + li, gn, ra, rm, rr);
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int il = row0_loc + a * 16 + 4 * lk + r;
-      const float ni = norms[(int64_t)I * T + il];
-      const PtStat si = pt_stat<PACK>((int64_t)I * T + il, gn, ra, rm, rr);
-      float v[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int jl = cl0 + c * 16 + li;
-        const float dd = (ni + norms[(int64_t)J * T + jl]) - 2.f * (acc[a][c][r] * inv_s2);
-        v[c] = tile_value<PACK>(fmaxf(dd, 0.f), diag, il, jl, si, sc[c]);
-      }
-      // the lane's four columns are the four elements of one float4 slot of
-      // the tile layout: one 16-byte store off the diagonal
-      if (!diag) {
-        *reinterpret_cast<float4 *>(tp + tile_pos(il, cl0 + li)) =
-            make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) put_d(tp, true, il, cl0 + c * 16 + li, v[c]);
-      }
-    }
-  }
-}
-
-// x3 modes: as k_tdist_lp, a workgroup covers 64 rows x 256 columns of the
-// tile; the sums come from the same routine as the stored path's.
-template <typename H, typename V8, bool PACK>
-__global__ __launch_bounds__(256, 2) void k_tdist_x3(const H *__restrict__ xs,
-                                                  const float2 *__restrict__ nhl, int32_t k32,
-                                                  int32_t bits, int32_t nb, int64_t tile0,
+template <int MODE, bool PACK>
+__global__ __launch_bounds__(256, 2) void k_tdist(TileSrc src, int32_t nb, int64_t tile0,
                                                   int64_t tile_base, float *__restrict__ Pb,
-                                                  const Hdr *guard, int64_t gn, int32_t gkey,
-                                                  const uint8_t *__restrict__ nz, bool skip,
-                                                  const float *__restrict__ ra,
-                                                  const float *__restrict__ rm,
-                                                  const float *__restrict__ rr) {
+                                                  int32_t gkey, const uint8_t *__restrict__ nz,
+                                                  bool skip) {
+  __shared__ RowStats<MODE> rows;
+  // a workspace prepared for another n, d or mode is flagged and left alone
+  if (!implicit_ready(src.h, src.n, gkey)) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+      flag_error(const_cast<Hdr *>(src.h), kErrState);
+    return;
+  }
   const int64_t tile = tile0 + blockIdx.x;
+  if (skip && !nz[tile]) return;
   int I, J;
-  if (!tdist_begin(guard, gn, gkey, nz, skip, tile, nb, I, J)) return;
-  const bool diag = (I == J);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int cl0 = w * 64;
-  const int64_t col0 = (int64_t)J * T + cl0;
-  const int row0_loc = blockIdx.y * 64;
-  const int64_t row0 = (int64_t)I * T + row0_loc;
-  const int li = l & 15, lk = l >> 4;
-  v4f A0[4][4], R[4][4];
-  x3_contract<H, V8>(xs, k32, row0, col0, li, lk, A0, R);
-  const X3Scale sc = x3_scale(guard, bits);
-  float *tp = Pb + (size_t)(tile - tile_base) * T * T;
-  PtStat scs[4];
-  float2 nj[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    scs[c] = pt_stat<PACK>(col0 + c * 16 + li, gn, ra, rm, rr);
-    nj[c] = nhl[col0 + c * 16 + li];
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int il = row0_loc + t * 16 + 4 * lk + r;
-      const float2 ni = nhl[(int64_t)I * T + il];
-      const PtStat si = pt_stat<PACK>((int64_t)I * T + il, gn, ra, rm, rr);
-      float v[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int jl = cl0 + c * 16 + li;
-        const float dd = x3_combine(ni, nj[c], A0[t][c][r], R[t][c][r], sc);
-        v[c] = tile_value<PACK>(dd, diag, il, jl, si, scs[c]);
-      }
-      if (!diag) {
-        *reinterpret_cast<float4 *>(tp + tile_pos(il, cl0 + li)) =
-            make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) put_d(tp, true, il, cl0 + c * 16 + li, v[c]);
-      }
-    }
-  }
+  tile_coords(tile, nb, I, J);
+  tile_strip<MODE, PACK>(src, I, J, blockIdx.y, Pb + (size_t)(tile - tile_base) * T * T, rows);
 }
 
 // ----------------------------------------------------------------------------
@@ -2923,52 +2462,50 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
   return hipGetLastError();
 }
 
+TileSrc tile_src(const Layout &L, void *ws) {
+  TileSrc s{};
+  s.h = at<const Hdr>(ws, L.hdr);
+  s.n = L.n;
+  s.npad = L.npad;
+  s.dpad = L.dpad;
+  s.kk = L.kk;
+  switch (L.mode) {
+    case TSNE_DIST_FP32:
+      s.x = at<const float>(ws, L.xfT);
+      s.norms = at<const float>(ws, L.norms32);
+      break;
+    case TSNE_DIST_BF16:
+    case TSNE_DIST_FP16:
+      s.x = at<const void>(ws, L.xa);
+      s.norms = at<const float>(ws, L.norms32);
+      break;
+    case TSNE_DIST_BF16X3:
+    case TSNE_DIST_FP16X3:
+      s.x = at<const void>(ws, L.xa);
+      s.norms = at<const float2>(ws, L.norms32);
+      s.kk = L.kk / 4;
+      s.bits = x3_bits(s.kk, L.mode == TSNE_DIST_BF16X3);
+      break;
+    default:
+      s.x = at<const double>(ws, L.xcT2);
+      s.norms = at<const double>(ws, L.norms2);
+  }
+  s.a = at<const float>(ws, L.a);
+  s.m = at<const float>(ws, L.m);
+  s.r = at<const float>(ws, L.r);
+  return s;
+}
+
 template <bool PACK>
 static void launch_tdist(const Layout &L, void *ws, int64_t tile0, int64_t count,
                          int64_t tile_base, bool skip_zero, hipStream_t st) {
-  const Hdr *h = at<const Hdr>(ws, L.hdr);
-  const int32_t key = implicit_key(L.d, L.mode);
-  const uint8_t *nz = at<const uint8_t>(ws, L.nz);
-  float *Pb = at<float>(ws, L.P);
-  const float *norms32 = at<const float>(ws, L.norms32);
-  const float *ra = at<const float>(ws, L.a), *rm = at<const float>(ws, L.m),
-              *rr = at<const float>(ws, L.r);
-  const dim3 g4((unsigned)count, T / 64);
-  switch (L.mode) {
-    case TSNE_DIST_FP32:
-      hipLaunchKernelGGL(k_tdist_f32<PACK>, g4, dim3(256), 0, st, at<const float>(ws, L.xfT),
-                         norms32, L.npad, L.dpad, L.nb, tile0, tile_base, Pb, h, L.n, key, nz,
-                         skip_zero, ra, rm, rr);
-      break;
-    case TSNE_DIST_BF16:
-      hipLaunchKernelGGL((k_tdist_lp<__bf16, v8bf, false, PACK>), g4, dim3(256), 0, st,
-                         at<const __bf16>(ws, L.xa), norms32, L.kk,
-                         L.nb, tile0, tile_base, Pb, h, L.n, key, nz, skip_zero, ra, rm, rr);
-      break;
-    case TSNE_DIST_FP16:
-      hipLaunchKernelGGL((k_tdist_lp<_Float16, v8h, true, PACK>), g4, dim3(256), 0, st,
-                         at<const _Float16>(ws, L.xa), norms32,
-                         L.kk, L.nb, tile0, tile_base, Pb, h, L.n, key, nz, skip_zero, ra, rm, rr);
-      break;
-    case TSNE_DIST_BF16X3:
-      hipLaunchKernelGGL((k_tdist_x3<__bf16, v8bf, PACK>), g4, dim3(256), 0, st,
-                         at<const __bf16>(ws, L.xa), at<const float2>(ws, L.norms32), L.kk / 4,
-                         x3_bits(L.kk / 4, true), L.nb, tile0, tile_base, Pb, h, L.n, key, nz,
-                         skip_zero, ra, rm, rr);
-      break;
-    case TSNE_DIST_FP16X3:
-      hipLaunchKernelGGL((k_tdist_x3<_Float16, v8h, PACK>), g4, dim3(256), 0, st,
-                         at<const _Float16>(ws, L.xa), at<const float2>(ws, L.norms32), L.kk / 4,
-                         x3_bits(L.kk / 4, false), L.nb, tile0, tile_base, Pb, h, L.n, key, nz,
-                         skip_zero, ra, rm, rr);
-      break;
-    default:
-      hipLaunchKernelGGL(k_tdist_f64<PACK>,
-                         dim3((unsigned)count, (T / 64) * (T / (64 * kTileCT))), dim3(256), 0, st,
-                         at<const double>(ws, L.xcT2), at<const double>(ws, L.norms2), L.npad,
-                         L.dpad, L.nb, tile0, tile_base, Pb, h, L.n, key, nz, skip_zero, ra, rm,
-                         rr);
-  }
+  const TileSrc src = tile_src(L, ws);
+  with_mode(L.mode, [&](auto mode) {
+    constexpr int M = decltype(mode)::value;
+    hipLaunchKernelGGL((k_tdist<M, PACK>), dim3((unsigned)count, tile_strips(M)), dim3(256), 0, st,
+                       src, L.nb, tile0, tile_base, at<float>(ws, L.P),
+                       implicit_key(L.d, L.mode), at<const uint8_t>(ws, L.nz), skip_zero);
+  });
 }
 
 hipError_t launch_implicit_tiles(const Layout &L, void *ws, int64_t tile0, int64_t count,

@@ -58,7 +58,7 @@ struct Hdr {
   double c_p;      // sum_{i != j} p_ij ln p_ij
   double p_sum;    // sum_{i != j} p_ij
   float xmax;      // max |centred x| (operand scaling of the FP16 modes)
-  float pad0;
+  int32_t next_tile;  // implicit P: next nonzero tile of the running force pass
   double pad[7];
 };
 static_assert(sizeof(Hdr) <= 256, "header must fit its slot");

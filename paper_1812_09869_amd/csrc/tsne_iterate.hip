@@ -21,6 +21,7 @@
 #include <mutex>
 
 #include "tsne_internal.h"
+#include "tsne_tile.h"
 
 namespace tsne {
 
@@ -344,6 +345,7 @@ __global__ __launch_bounds__(256) void k_gather_y(const float2 *__restrict__ Y,
                                                   float2 *__restrict__ Yp,
                                                   float4 *__restrict__ extent, Hdr *h) {
   if (!state_ok(h, n)) return;  // the layout of another n: touch nothing
+  if (blockIdx.x == 0 && threadIdx.x == 0) h->next_tile = 0;
   gather_rows(Y, perm, n, Yp, extent, blockIdx.x);
 }
 
@@ -576,12 +578,14 @@ __global__ __launch_bounds__(256, 2) void k_force_any(const float4 *__restrict__
                                                       int32_t nb, float4 *__restrict__ part,
                                                       float *__restrict__ zpart,
                                                       const int2 *__restrict__ tmap,
-                                                      const uint8_t *__restrict__ nz, Hdr *h) {
+                                                      const uint8_t *__restrict__ nz,
+                                                      int32_t key, Hdr *h) {
   __shared__ union {
     ForceSmem full;
     ZeroSmem zero;
   } sm;
-  if (!ready_is(h, n, 1)) {
+  // key: that of implicit P (then P is the buffer, just filled), negative for stored P
+  if (key < 0 ? !ready_is(h, n, 1) : !ready_is(h, n, 2) || implicit_key(h->d, h->mode) != key) {
     if (blockIdx.x == 0 && threadIdx.x == 0) flag_error(h, kErrState);
     return;
   }
@@ -596,26 +600,56 @@ __global__ __launch_bounds__(256, 2) void k_force_any(const float4 *__restrict__
   }
 }
 
-// Implicit P: the nonzero tiles among tile0 .. tile0 + gridDim.x - 1 (whole
-// block rows), whose P was just recomputed into the buffer Pb (tile
-// tile0 + x at slot x); the all-zero ones are k_force_zero's.
-__global__ __launch_bounds__(256, 2) void k_force_range(const float4 *__restrict__ Pb,
-                                                        const float2 *__restrict__ Y, int64_t n,
-                                                        int32_t nb, float4 *__restrict__ part,
-                                                        float *__restrict__ zpart,
-                                                        const int2 *__restrict__ tmap,
-                                                        const uint8_t *__restrict__ nz,
-                                                        int64_t tile0, int32_t key, Hdr *h) {
-  __shared__ ForceSmem sm;
+// Implicit P of a set whose triangle the buffer does not hold: persistent over the
+// nonzero tiles of the list, a workgroup recomputes a tile's P into its own
+// slot of the buffer and runs the tile body on it while it is still in the
+// caches; nothing of a tile outlives its workgroup's turn. Tiles are taken from a counter
+// (set to 0 by the gather before it): half of the workgroups start beside the
+// all-zero kernel, half behind it. Every tile's results are its own, so the
+// order does not matter.
+// What bounds it is the latency of a strip's operand loads at two waves per
+// SIMD. One launch for the tiles' P and one for the forces per buffer of 2,048
+// consecutive tiles spent most of their time starting workgroups of zero
+// tiles, and waiting for one another: at n = 65,536 (4,620 of 32,896 tiles
+// nonzero, x3 operands) a pass took 17 x (68 + 27) us and 550 us of the all-zero
+// kernel, an iteration 2,474 us; now 1,300 (static shares of the list: 1,580; all
+// workgroups at once: 1,473).
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void k_force_implicit(
+    TileSrc src, float4 *__restrict__ Pb, const float2 *__restrict__ Y, int64_t n, int32_t nb,
+    float4 *__restrict__ part, float *__restrict__ zpart, const int32_t *__restrict__ tlist,
+    const int32_t *__restrict__ tcount, const int2 *__restrict__ tmap, int32_t slot0, int32_t key,
+    Hdr *h) {
+  __shared__ int32_t next;
+  __shared__ union {
+    RowStats<MODE> rows;
+    ForceSmem full;
+  } sm;
   if (!ready_is(h, n, 2) || implicit_key(h->d, h->mode) != key) {
     if (blockIdx.x == 0 && threadIdx.x == 0) flag_error(h, kErrState);
     return;
   }
-  const int64_t tile = tile0 + blockIdx.x;
-  if (!nz[tile]) return;
-  float2 yc[16];
-  const TileCtx c = tile_begin(Y, n, nb, tmap, tile, yc, sm);
-  full_tile_body(c, yc, Pb, part, nb, zpart, tile, blockIdx.x, sm);
+  float4 *slot = Pb + (size_t)(slot0 + blockIdx.x) * TT4;
+  const int32_t count = tcount[1], first = tcount[0];
+  for (;;) {
+    if (threadIdx.x == 0) next = atomicAdd(&h->next_tile, 1);
+    __syncthreads();  // also: the last tile's LDS is free
+    const int32_t i = next;
+    if (i >= count) return;
+    const int64_t tile = tlist[first + i];
+    const int2 ij = tmap[tile];
+    for (int s = 0; s < tile_strips(MODE); ++s) {
+      tile_strip<MODE, true>(src, ij.x, ij.y, s, reinterpret_cast<float *>(slot), sm.rows);
+      __syncthreads();  // the statistics of the next strip
+    }
+    // every wave's stores are done before any wave loads from the slot
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    float2 yc[16];
+    const TileCtx c = tile_begin(Y, n, nb, tmap, tile, yc, sm.full);
+    full_tile_body(c, yc, slot, part, nb, zpart, tile, 0, sm.full);
+    __syncthreads();
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -1925,7 +1959,8 @@ hipError_t launch_force(const Layout &L, void *ws, const float *y, hipStream_t s
   float *zp = at<float>(ws, L.zpart);
   if (L.nt <= kAnyTiles) {
     hipLaunchKernelGGL(k_force_any, dim3((unsigned)L.nt), dim3(256), 0, st, at<const float4>(ws, L.P),
-                       (const float2 *)yp, L.n, L.nb, part, zp, tm, at<const uint8_t>(ws, L.nz), h);
+                       (const float2 *)yp, L.n, L.nb, part, zp, tm, at<const uint8_t>(ws, L.nz), -1,
+                       h);
     return hipGetLastError();
   }
   const unsigned full_grid = (unsigned)(L.nt < kFullGrid ? L.nt : kFullGrid);
@@ -1945,53 +1980,61 @@ hipError_t launch_force(const Layout &L, void *ws, const float *y, hipStream_t s
   return hipStreamWaitEvent(st, ss->join, 0);
 }
 
-// Implicit P: the all-zero tiles (known since the affinity stage) in one
-// repulsion-only launch on the side stream, as in the stored path; beside it,
-// per buffer of block rows, the nonzero tiles' packed P recomputed by one
-// tile-distance launch (zero tiles skipped) and the full tile body on them.
-// The two write disjoint partial-sum slots. The slot lists and the sums of P
-// are those of the affinity stage.
+// Implicit P. Up to kImplicitTiles tiles the buffer holds the whole triangle: one
+// launch for the nonzero tiles' P (in strips of 64 rows, so that a small set
+// fills the chip) and the force launch of a stored P on it. An iteration of
+// 4,000 points takes 64 us so (tile by tile in one launch 103), 9,000 points
+// 103 (113), 16,000 148 (172). Larger sets go tile by tile (20,000 points,
+// 3,160 tiles: 268 us, by buffers of tiles 358), the all-zero tiles (known since
+// the affinity stage) beside them on the side stream as in the stored path; the
+// two write disjoint partial-sum slots. The slot lists and the sums of P are
+// those of the affinity stage.
 hipError_t launch_force_implicit(const Layout &L, void *ws, const float *y, hipStream_t st) {
-  if (L.split > 1) {
-    // the buffer holds the whole triangle (at most 136 tiles): one round
-    static_assert(kSplitNb * (kSplitNb + 1) / 2 <= kImplicitTiles, "a split problem fits");
-    hipError_t e = launch_implicit_tiles(L, ws, 0, L.nt, 0, true, true, st);
-    return e != hipSuccess ? e
-                           : launch_force_units(L, ws, y, implicit_key(L.d, L.mode), st);
-  }
+  const int32_t key = implicit_key(L.d, L.mode);
+  static_assert(kSplitNb * (kSplitNb + 1) / 2 <= kImplicitTiles, "a split problem fits");
+  hipError_t e = hipSuccess;
+  if (L.nt <= kImplicitTiles &&
+      (e = launch_implicit_tiles(L, ws, 0, L.nt, 0, true, true, st)) != hipSuccess)
+    return e;
+  if (L.split > 1) return launch_force_units(L, ws, y, key, st);
   Hdr *h = at<Hdr>(ws, L.hdr);
   float2 *yp = at<float2>(ws, L.yp);
   hipLaunchKernelGGL(k_gather_y, dim3(L.nb), dim3(256), 0, st, reinterpret_cast<const float2 *>(y),
                      at<const int32_t>(ws, L.perm), L.n, yp, at<float4>(ws, L.extent), h);
   float4 *part = at<float4>(ws, L.part);
   float *zp = at<float>(ws, L.zpart);
+  const int32_t *tl = at<const int32_t>(ws, L.tlist), *tc = at<const int32_t>(ws, L.tcount);
   const int2 *tm = at<const int2>(ws, L.tmap);
+  if (L.nt <= kImplicitTiles) {
+    static_assert(kImplicitTiles <= kAnyTiles, "one launch for both kinds of tile");
+    hipLaunchKernelGGL(k_force_any, dim3((unsigned)L.nt), dim3(256), 0, st, at<const float4>(ws, L.P),
+                       (const float2 *)yp, L.n, L.nb, part, zp, tm, at<const uint8_t>(ws, L.nz), key,
+                       h);
+    return hipGetLastError();
+  }
+  const TileSrc src = tile_src(L, ws);
+  auto launch = [&](int64_t wgs, int32_t slot0, hipStream_t q) {
+    with_mode(L.mode, [&](auto mode) {
+      hipLaunchKernelGGL(k_force_implicit<decltype(mode)::value>, dim3((unsigned)wgs), dim3(256), 0,
+                         q, src, at<float4>(ws, L.P), (const float2 *)yp, L.n, L.nb, part, zp, tl,
+                         tc, tm, slot0, key, h);
+    });
+    return hipGetLastError();
+  };
   std::lock_guard<std::mutex> lock(g_side_mu);
   SideStream *ss = nullptr;
-  hipError_t e = side_stream(ss);
-  if (e != hipSuccess) return e;
+  if ((e = side_stream(ss)) != hipSuccess) return e;
   if ((e = hipEventRecord(ss->fork, st)) != hipSuccess) return e;
+  // one workgroup per CU beside the all-zero kernel, a second one behind it
+  constexpr int64_t half = kFullGrid / 2;
+  static_assert(2 * half <= kImplicitTiles, "a slot of the buffer to each workgroup");
+  if ((e = launch(half, 0, st)) != hipSuccess) return e;
   if ((e = hipStreamWaitEvent(ss->s, ss->fork, 0)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_force_zero, dim3((unsigned)L.nt), dim3(256), 0, ss->s, (const float2 *)yp,
-                     L.n, L.nb, part, zp, at<const int32_t>(ws, L.tlist),
-                     at<const int32_t>(ws, L.tcount), tm, h, 2);
+                     L.n, L.nb, part, zp, tl, tc, tm, h, 2);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch(half, half, ss->s)) != hipSuccess) return e;
   if ((e = hipEventRecord(ss->join, ss->s)) != hipSuccess) return e;
-  const int64_t cap = implicit_capacity(L);
-  for (int b0 = 0; b0 < L.nb;) {
-    // the block rows whose tiles fill the buffer (at least one)
-    int b1 = b0 + 1;
-    while (b1 < L.nb && tile_start(b1 + 1, L.nb) - tile_start(b0, L.nb) <= cap) ++b1;
-    const int64_t base = tile_start(b0, L.nb), count = tile_start(b1, L.nb) - base;
-    // the nonzero tiles' P, packed as the distances are formed
-    if ((e = launch_implicit_tiles(L, ws, base, count, base, true, true, st)) != hipSuccess)
-      return e;
-    hipLaunchKernelGGL(k_force_range, dim3((unsigned)count), dim3(256), 0, st,
-                       at<const float4>(ws, L.P), (const float2 *)yp, L.n, L.nb, part, zp, tm,
-                       at<const uint8_t>(ws, L.nz), base, implicit_key(L.d, L.mode), h);
-    b0 = b1;
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   return hipStreamWaitEvent(st, ss->join, 0);
 }
 
