@@ -122,6 +122,25 @@ __global__ __launch_bounds__(256) void k_centre(const float *__restrict__ x, int
     atomicMax(reinterpret_cast<unsigned int *>(&h->xmax), __float_as_uint(amax));
 }
 
+// Place of a workgroup of a distance launch: column strip x of nx, 64-row strip
+// of row block z of the group. Consecutive workgroups go to the eight XCDs in
+// turn, so the strips of an XCD's turn are the row strips of one column strip:
+// its columns come into that XCD's L2 once (in row-major order every row strip
+// read all columns anew, 4.2 MB an XCD at n = 65,536 against 4 MB of L2). The
+// affinity stage there: 23.4 ms, so 22.7; the FP64 kernel, whose strips are half as
+// wide and which is bound by its MFMAs, keeps the row order (29.1 against 31.0).
+// False for the padding workgroups of the last turn. Grid: dist_grid.
+__device__ __forceinline__ bool dist_place(int nx, int blocks, int &x, int &row0, int &z) {
+  const unsigned rows = (unsigned)blocks * (T / 64), k = blockIdx.x / 8;
+  x = (int)(8 * (k / rows) + blockIdx.x % 8);
+  row0 = 64 * (int)(k % rows % (T / 64));
+  z = (int)(k % rows / (T / 64));
+  return x < nx;
+}
+static dim3 dist_grid(int64_t nx, int blocks) {
+  return dim3((unsigned)((nx + 7) / 8 * 8 * blocks * (T / 64)));
+}
+
 // ----------------------------------------------------------------------------
 // 2a. Distance block on FP64 MFMA: rows b*T .. b*T+T-1 against all columns.
 //
@@ -456,20 +475,23 @@ template <typename H, typename V8>
 __global__ __launch_bounds__(256, 2) void k_dist_x3(const H *__restrict__ xs,
                                                  const float2 *__restrict__ nhl, int64_t npad,
                                                  int32_t k32, int32_t bits, int32_t b,
-                                                 float *__restrict__ dblock, const Hdr *h,
-                                                 float4 *__restrict__ P, int32_t nb) {
-  b += blockIdx.z;
-  dblock += (size_t)blockIdx.z * T * npad;
+                                                 int32_t blocks, float *__restrict__ dblock,
+                                                 const Hdr *h, float4 *__restrict__ P,
+                                                 int32_t nb) {
+  int strip, row0_loc, z;
+  if (!dist_place(nb, blocks, strip, row0_loc, z)) return;
+  b += z;
+  dblock += (size_t)z * T * npad;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   // column tile, rotated so that the diagonal one (the workgroups with the
   // most stores) is dispatched first
-  const int J = (int)((blockIdx.x + (unsigned)b) % gridDim.x);
+  const int J = (int)((unsigned)(strip + b) % (unsigned)nb);
   const int64_t col0 = (int64_t)J * 256 + w * 64;
-  const int row0_loc = blockIdx.y * 64;
   const int64_t row0 = (int64_t)b * T + row0_loc;
   const int li = l & 15, lk = l >> 4;
   v4f A0[4][4], R[4][4];
-  x3_contract<H, V8>(xs, k32, row0, col0, li, lk, A0, R);
+  __shared__ X3Smem<V8> sm;
+  x3_contract<H, V8>(xs, k32, row0, col0, threadIdx.x, A0, R, sm);
   const X3Scale sc = x3_scale(h, bits);
   // every norm is loaded before the first store, so no store waits on a load
   float2 nj[4], ni[4][4];
@@ -2176,14 +2198,14 @@ static bool launch_dist(const Layout &L, void *ws, int b, int blocks, const doub
                          L.npad, L.kk, b, dblock, h);
       break;
     case TSNE_DIST_BF16X3:
-      hipLaunchKernelGGL((k_dist_x3<__bf16, v8bf>), dgrid, dim3(256), 0, st,
+      hipLaunchKernelGGL((k_dist_x3<__bf16, v8bf>), dist_grid(L.nb, blocks), dim3(256), 0, st,
                          at<const __bf16>(ws, L.xa), at<const float2>(ws, L.norms32), L.npad,
-                         L.kk / 4, x3_bits(L.kk / 4, true), b, dblock, h, P, L.nb);
+                         L.kk / 4, x3_bits(L.kk / 4, true), b, blocks, dblock, h, P, L.nb);
       return P != nullptr;
     case TSNE_DIST_FP16X3:
-      hipLaunchKernelGGL((k_dist_x3<_Float16, v8h>), dgrid, dim3(256), 0, st,
+      hipLaunchKernelGGL((k_dist_x3<_Float16, v8h>), dist_grid(L.nb, blocks), dim3(256), 0, st,
                          at<const _Float16>(ws, L.xa), at<const float2>(ws, L.norms32), L.npad,
-                         L.kk / 4, x3_bits(L.kk / 4, false), b, dblock, h, P, L.nb);
+                         L.kk / 4, x3_bits(L.kk / 4, false), b, blocks, dblock, h, P, L.nb);
       return P != nullptr;
     default:
       hipLaunchKernelGGL(k_dist_f64,

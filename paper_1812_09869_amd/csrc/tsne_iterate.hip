@@ -1835,7 +1835,7 @@ __global__ __launch_bounds__(256, 2) void k_cost(const float4 *__restrict__ P,
   cost_wg(P, Y, n, nb, cpart, nz, h, blockIdx.x, blockIdx.x, 1);
 }
 
-// Implicit P: the cost terms of the tiles in the buffer (see k_force_range).
+// Implicit P: the cost terms of the tiles in the buffer.
 __global__ __launch_bounds__(256, 2) void k_cost_range(const float4 *__restrict__ Pb,
                                                        const float2 *__restrict__ Y, int64_t n,
                                                        int32_t nb, double2 *__restrict__ cpart,

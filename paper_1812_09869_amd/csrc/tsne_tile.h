@@ -87,50 +87,65 @@ __device__ __forceinline__ v4f mfma16x32(V8 a, V8 b, v4f c) {
 // The two sums A0 and R of a 64 x 64 block (4 x 4 MFMA tiles): rows ra .. ra+63
 // against columns cb .. cb+63. Stored and recomputed P call this same routine,
 // so their sums agree bit for bit.
+// The workgroup's 64 rows are the same for its waves and pass through LDS (one
+// coalesced load of 16 KB per 32 values of k, the next while this one is used; a
+// row's pitch of 17 pieces spreads 16 rows over all banks); a wave's columns of
+// one K step are in flight at once. With the fragments loaded where they were
+// used, ten waits for memory a strip were what bounded it at two waves per SIMD:
+// 1,024 rows of 65,536, 64 values of k: 166 us,
+// now 146.
+template <typename V8>
+struct X3Smem {
+  V8 a[2][64][17];
+};
 template <typename H, typename V8>
 __device__ __forceinline__ void x3_contract(const H *__restrict__ xs, int32_t k32, int64_t ra,
-                                            int64_t cb, int li, int lk, v4f (&A0)[4][4],
-                                            v4f (&R)[4][4]) {
+                                            int64_t cb, int t, v4f (&A0)[4][4], v4f (&R)[4][4],
+                                            X3Smem<V8> &sm) {
   const int64_t kk = 4 * (int64_t)k32;
+  const int li = t & 15, lk = (t >> 4) & 3;  // also: piece li of row t / 16 (+ 16, 32, 48)
+  const H *pa = xs + (ra + (t >> 4)) * kk + 8 * li, *pb = xs + (cb + li) * kk + 8 * lk;
+  V8 st[4], b[4][4];  // staged rows; [slice][column tile]: h1, h2, 2^-b h2, 2^-b h3
+  auto load_rows = [&](int64_t off) {
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+    for (int u = 0; u < 4; ++u) st[u] = *reinterpret_cast<const V8 *>(pa + 16 * u * kk + off);
+  };
+  auto load_cols = [&](int64_t off) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      A0[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-      R[t][c] = A0[t][c];
-    }
-  for (int k0 = 0; k0 < k32; k0 += 32) {
-    const int64_t off = (int64_t)(k0 >> 5) * 128 + 8 * lk;
-    V8 a[4][4];  // [slice][row tile]: h1, h2, 2^-b h2, 2^-b h3
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        a[q][t] = *reinterpret_cast<const V8 *>(xs + (ra + 16 * t + li) * kk + off + 32 * q);
+        b[q][c] = *reinterpret_cast<const V8 *>(pb + 16 * c * kk + off + 32 * q);
+  };
+  auto step = [&](auto first, int k0, int buf) {
+    const int64_t next = (int64_t)((k0 >> 5) + 1) * 128;
+    const v4f zero = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      V8 bv[4];
+    for (int u = 0; u < 4; ++u) sm.a[buf][(t >> 4) + 16 * u][li] = st[u];
+    __syncthreads();
+    if (k0 + 32 < k32) load_rows(next);
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        bv[q] = *reinterpret_cast<const V8 *>(xs + (cb + 16 * c + li) * kk + off + 32 * q);
+    for (int u = 0; u < 4; ++u) {
+      V8 a[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) A0[t][c] = mfma16x32<H, V8>(a[0][t], bv[0], A0[t][c]);
+      for (int q = 0; q < 4; ++q) a[q] = sm.a[buf][16 * u + li][4 * q + lk];
+      constexpr int kRows[7] = {0, 1, 0, 1, 3, 2, 3}, kCols[7] = {1, 0, 3, 2, 0, 3, 2};
 #pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[0][t], bv[1], R[t][c]);
+      for (int c = 0; c < 4; ++c)
+        A0[u][c] = mfma16x32<H, V8>(a[0], b[0][c], decltype(first)::value ? zero : A0[u][c]);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[1][t], bv[0], R[t][c]);
+      for (int p = 0; p < 7; ++p)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[0][t], bv[3], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[1][t], bv[2], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[3][t], bv[0], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[2][t], bv[3], R[t][c]);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) R[t][c] = mfma16x32<H, V8>(a[3][t], bv[2], R[t][c]);
+        for (int c = 0; c < 4; ++c)
+          R[u][c] = mfma16x32<H, V8>(a[kRows[p]], b[kCols[p]][c],
+                                     decltype(first)::value && p == 0 ? zero : R[u][c]);
     }
-  }
+    if (k0 + 32 < k32) load_cols(next);
+  };
+  load_rows(0);
+  load_cols(0);
+  step(std::true_type{}, 0, 0);
+  for (int k0 = 32, buf = 1; k0 < k32; k0 += 32, buf ^= 1) step(std::false_type{}, k0, buf);
 }
 
 // 2 sigma^2 and 2 sigma^2 2^-b
@@ -203,7 +218,8 @@ __device__ __forceinline__ PtStat pt_stat(int64_t g, int64_t n, const float *__r
   return p;
 }
 
-// Norms and statistics of a strip's 64 rows, in LDS for its epilogue: loads and
+// Norms and statistics of a strip's 64 rows (and the x3 modes' staged operands),
+// in LDS for its epilogue: loads and
 // stores of a wave complete in order, so statistics loaded between the stores
 // of the rows before them would wait for those stores.
 template <int MODE>
@@ -214,6 +230,10 @@ struct RowStats {
                                                   float2, float>>;
   N norm[64];
   float4 st[64];  // a, m, r; w is 1 for a point, 0 for padding
+  struct None {};
+  std::conditional_t<MODE == TSNE_DIST_BF16X3, X3Smem<v8bf>,
+                     std::conditional_t<MODE == TSNE_DIST_FP16X3, X3Smem<v8h>, None>>
+      x3;
 };
 
 // The stored value of one element: the distance, or with PACK its p_ij (the
@@ -278,7 +298,7 @@ __device__ __forceinline__ void tile_strip(const TileSrc &src, int I, int J, int
   V4 acc[4][CT];
   v4f R[X3 ? 4 : 1][4];
   if constexpr (X3) {
-    x3_contract<H, V8>(static_cast<const H *>(src.x), src.kk, row0, col0, li, lk, acc, R);
+    x3_contract<H, V8>(static_cast<const H *>(src.x), src.kk, row0, col0, t, acc, R, rows.x3);
   } else {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
