@@ -674,7 +674,7 @@ __global__ __launch_bounds__(kCalThreads) void k_calibrate(const float *__restri
 #pragma unroll
       for (int q = 0; q < VPT; ++q) {
         const int jq = q * kCalThreads;
-        v[q] = row[(jq + j0 < nn ? jq : 0) + tid];
+        v[q] = row[jq + j0 < nn ? jq + tid : ln];  // (past n: any column there is)
       }
     }
 #pragma unroll
