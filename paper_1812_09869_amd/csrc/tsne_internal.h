@@ -23,7 +23,7 @@ namespace tsne {
 // e = 0..3, so every wave-wide float4 load is one contiguous 1 KiB segment.
 // ---------------------------------------------------------------------------
 constexpr int kMeanPartsPerBlock = 4;  // re-centring partial sums per row block (at most)
-constexpr int64_t kImplicitTiles = 2048;  // implicit P: tiles recomputed per force launch (at least)
+constexpr int64_t kImplicitTiles = 2048;  // implicit P: tiles of the buffer (at least)
 constexpr int T = 256;             // tile edge
 constexpr int TT4 = T * T / 4;     // float4 per tile
 constexpr int kThreads = 256;      // threads per tile workgroup
