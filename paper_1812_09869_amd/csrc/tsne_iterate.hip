@@ -394,7 +394,8 @@ __device__ __forceinline__ TileCtx tile_begin(const float2 *__restrict__ Y, int6
 }
 
 // A tile whose stored P is all zero: repulsion and Z only, no P traffic,
-// float2 accumulators. Ends with a workgroup barrier.
+// float2 accumulators. Ends with reads of colbuf2 and zred and no barrier: a
+// workgroup that goes on to another tile needs one first.
 template <class Smem>
 __device__ __forceinline__ void zero_tile_body(const TileCtx &c, const float2 (&yc)[16],
                                                float4 *__restrict__ part,
@@ -445,7 +446,9 @@ __device__ __forceinline__ void zero_tile_body(const TileCtx &c, const float2 (&
 }
 
 // A tile with nonzero P: attraction and repulsion, P streamed through the
-// per-wave LDS rings. Ends with a workgroup barrier.
+// per-wave LDS rings. Ends with reads of colbuf and zred and no barrier: a next
+// tile with the same LDS layout writes neither before tile_begin's barrier, any
+// other use of the LDS needs a barrier first.
 __device__ __forceinline__ void full_tile_body(const TileCtx &c, const float2 (&yc)[16],
                                                const float4 *__restrict__ P,
                                                float4 *__restrict__ part, int32_t nb,
@@ -1531,18 +1534,21 @@ __device__ inline void full_range(const BatchEntry &e, int64_t &first, int64_t &
   cnt = min(max((int64_t)e.tcount[1], (int64_t)0), e.nt - first);
 }
 
-// One tile with P. Ends with a workgroup barrier.
+// One tile with P. The barrier at the end stands between this tile's last reads
+// of the LDS and the first writes of the workgroup's next tile, which may be of
+// the other kind: the units' row positions lie where a whole tile's column sums
+// are read, and the reverse.
 __device__ __forceinline__ void full_tile_of(const BatchEntry &e, int64_t tile,
                                              BatchSmem<ForceSmem> &sm) {
   if (e.split > 1) {
     unit_body<1>(e.P, e.yp, nullptr, e.n, e.nb, e.part, e.zpart, nullptr, e.tmap[tile], true, tile,
                  tile, 0, kUnits, sm.unit);
-    __syncthreads();
-    return;
+  } else {
+    float2 yc[16];
+    const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm.tile);
+    full_tile_body(c, yc, e.P, e.part, e.nb, e.zpart, tile, tile, sm.tile);
   }
-  float2 yc[16];
-  const TileCtx c = tile_begin(e.yp, e.n, e.nb, e.tmap, tile, yc, sm.tile);
-  full_tile_body(c, yc, e.P, e.part, e.nb, e.zpart, tile, tile, sm.tile);
+  __syncthreads();
 }
 
 // Problems whose list offsets a workgroup of the nonzero-tile kernel keeps in
