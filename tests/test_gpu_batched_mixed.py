@@ -49,3 +49,16 @@ def test_small_problems_after_large_ones():
     for _ in range(46):
         ns += [int(rng.integers(2049, 4300)), int(rng.integers(1200, 2049))]
     _compare(ns, range(len(ns)), 4, 52)
+
+
+def test_more_than_1024_problems_of_both_kinds():
+    """1,030 problems, six of them large: more than the kernel keeps the table of in LDS (1,024),
+    so it walks the table. The large ones, their neighbours and others on both sides of the 1,024
+    boundary are compared."""
+    rng = np.random.Generator(np.random.PCG64(53))
+    ns = [int(v) for v in rng.integers(40, 300, 1030)]
+    large = {0: 14000, 300: 2049, 700: 7000, 1023: 9000, 1025: 2300, 1029: 4097}
+    for k, n in large.items():
+        ns[k] = n
+    chosen = sorted({min(max(k + o, 0), 1029) for k in large for o in (-1, 0, 1)} | {511})
+    _compare(ns, chosen, 3, 54)
