@@ -889,8 +889,10 @@ struct RowSearch {
 };
 
 // v: the distances of the wave's rows, VPT per lane, INFINITY where excluded
-// (shifted by the row minimum in place). ok: the lane's row exists.
-template <int VPT, int R>
+// (shifted by the row minimum in place). ok: the lane's row exists. G: points of a
+// lane that are summed in FP32 before their sum goes to FP64 (fewer than VPT: in two
+// alternating sums, as in k_calibrate).
+template <int VPT, int R, int G>
 __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, bool ok,
                                                  double logu, int max_bisect, double tol_h) {
   const int g = R == 4 ? (threadIdx.x & 63) >> 4 : 0;
@@ -940,18 +942,23 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f.a), 16 * r));
-      float s = 0.f, tt = 0.f, qq = 0.f;
+      SS[r] = TT[r] = QQ[r] = 0.0;
 #pragma unroll
-      for (int q = 0; q < VPT; ++q) {
-        const float ex = __builtin_amdgcn_exp2f(-ar * v[r][q]);
-        const float ve = v[r][q] * ex;  // 0 for an excluded entry (ex = 0)
-        s += ex;
-        tt += ve;
-        qq = fmaf(v[r][q], ve, qq);
+      for (int q0 = 0; q0 < VPT; q0 += G) {
+        float s[2] = {}, tt[2] = {}, qq[2] = {};
+#pragma unroll
+        for (int q = q0; q < q0 + G; ++q) {
+          const int o = G < VPT ? q & 1 : 0;
+          const float ex = __builtin_amdgcn_exp2f(-ar * v[r][q]);
+          const float ve = v[r][q] * ex;  // 0 for an excluded entry (ex = 0)
+          s[o] += ex;
+          tt[o] += ve;
+          qq[o] = fmaf(v[r][q], ve, qq[o]);
+        }
+        SS[r] += (double)(s[0] + s[1]);
+        TT[r] += (double)(tt[0] + tt[1]);
+        QQ[r] += (double)(qq[0] + qq[1]);
       }
-      SS[r] = (double)s;
-      TT[r] = (double)tt;
-      QQ[r] = (double)qq;
     }
     const double ss = rows_sum_d<R>(SS), ts = rows_sum_d<R>(TT), qs = rows_sum_d<R>(QQ);
     if (f.done) continue;
@@ -989,10 +996,11 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
 // many-problem path, instead of a workgroup of 1,024 threads to a row, most of
 // whose time at two points a thread went into its barriers and wave sums. All
 // rows of the problem in one launch (their distances fit in one group), each
-// from its own start. n = 2,000: 19 us against 149 (two launches).
+// from its own start. n = 2,000: 19 us against 149 (two launches). G: a workgroup to
+// a row had 1, 2 or 4 points a thread, summed in FP32, and all else in FP64; so here.
 constexpr int64_t kCalWaveN = 4096;
 constexpr int kCalWaves = 4;  // waves per workgroup
-template <int VPT, int R>
+template <int VPT, int R, int G>
 __global__ __launch_bounds__(kCalWaves * 64) void k_calibrate_wave(
     const float *__restrict__ dblock, int64_t n, int64_t npad, int32_t b, double logu,
     int max_bisect, double tol_h, CalOut out, Hdr *h) {
@@ -1012,7 +1020,7 @@ __global__ __launch_bounds__(kCalWaves * 64) void k_calibrate_wave(
     }
   }
   const int g = R == 4 ? l >> 4 : 0;
-  const RowSearch f = search_rows<VPT, R>(v, n, i0 + g < n, logu, max_bisect, tol_h);
+  const RowSearch f = search_rows<VPT, R, G>(v, n, i0 + g < n, logu, max_bisect, tol_h);
   if ((R == 4 ? (l & 15) : l) == 0 && i0 + g < n) f.store(out, i0 + g, n, false, h);
 }
 
@@ -2211,7 +2219,8 @@ __global__ __launch_bounds__(kSmallWaves * 64) void k_small_calibrate(
   }
   if (i0 >= n) return;  // no barrier below this point
   const int g = R == 4 ? l >> 4 : 0;
-  const RowSearch f = search_rows<VPT, R>(v, n, i0 + g < n, log(e.perplexity), max_bisect, tol_h);
+  const RowSearch f =
+      search_rows<VPT, R, VPT>(v, n, i0 + g < n, log(e.perplexity), max_bisect, tol_h);
   bool any_bad = false;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -2431,23 +2440,23 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
     const int rows = (int)(left < span ? left : span);
     dim3 g(rows), blk(kCalThreads);
     if (L.n <= kCalWaveN && !stats_only) {
-#define TSNE_CAL(V, R)                                                                          \
-  hipLaunchKernelGGL((k_calibrate_wave<V, R>),                                                  \
+#define TSNE_CAL(V, R, G)                                                                       \
+  hipLaunchKernelGGL((k_calibrate_wave<V, R, G>),                                               \
                      dim3((unsigned)((rows + kCalWaves * R - 1) / (kCalWaves * R))),            \
                      dim3(kCalWaves * 64), 0, st, dblock, L.n, L.npad, b, logu, max_bisect,     \
                      tol_h, co, h)
       // (rows to a wave as in small_rows: distances of four rows stay in
       // registers up to 16 a lane)
       if (L.n <= 256)
-        TSNE_CAL(4, 4);
+        TSNE_CAL(4, 4, 1);
       else if (L.n <= 512)
-        TSNE_CAL(8, 4);
+        TSNE_CAL(8, 4, 1);
       else if (L.n <= 1024)
-        TSNE_CAL(16, 4);
+        TSNE_CAL(16, 4, 1);
       else if (L.n <= 2048)
-        TSNE_CAL(32, 1);
+        TSNE_CAL(32, 1, 2);
       else
-        TSNE_CAL(64, 1);
+        TSNE_CAL(64, 1, 4);
 #undef TSNE_CAL
       return;
     }
