@@ -1413,18 +1413,25 @@ __device__ inline const BatchEntry *batch_table(const BatchHdr *bh) {
                                               kBatchHdrBytes);
 }
 
-// Last entry whose first unit is not after `key`. Every wave looks at 64
-// entries at a time (one load each), so the search is one or two memory
-// latencies instead of one per halving. Problems that are not split have no
-// units: they share their successor's first unit and are never the last; a
-// run of them at the end of the table starts past every unit.
+// Last entry whose first unit is not after `key`, entry 0's being 0. The wave looks
+// at 128 entries at a time (two loads a lane, in flight together) and goes on
+// between two of them: one memory latency up to 128 problems, two up to 16,384,
+// three beyond, where halving takes seven for 128. Problems that are not split
+// have no units: they share their successor's first unit and are never the last;
+// a run of them at the end of the table starts past every unit.
 __device__ inline int find_unit_entry(const BatchEntry *tab, int count, int64_t key) {
-  int below = 0;
-  for (int b = 0; b < count; b += 64) {
-    const int p = b + (threadIdx.x & 63);
-    below += __popcll(__ballot(p < count && tab[p].unit0 <= key));
+  const int l = threadIdx.x & 63;
+  int lo = 0, len = count;
+  while (len > 1) {
+    const int step = (len + 127) / 128;
+    const int64_t p0 = (int64_t)l * step, p1 = (int64_t)(l + 64) * step;
+    const bool below0 = p0 < len && tab[lo + p0].unit0 <= key;
+    const bool below1 = p1 < len && tab[lo + p1].unit0 <= key;
+    const int at = (__popcll(__ballot(below0)) + __popcll(__ballot(below1)) - 1) * step;
+    lo += at;
+    len = min(step, len - at);
   }
-  return below > 0 ? below - 1 : 0;
+  return lo;
 }
 
 // Units of the split problems, `per` (1, 2 or 4) of one tile to a workgroup.
