@@ -62,10 +62,13 @@ __global__ __launch_bounds__(64 * kKdeWaves) void k_kde_raster(const float2 *__r
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.0;
   float4 *pts = sm.pts[w];
-  auto fetch = [&](int64_t j) {  // points past the end: weight 0
-    const float2 p = j < n ? y[j] : make_float2(0.f, 0.f);
-    const double b = j < n ? beta[j] : 0.0;
-    return make_float4(p.x, p.y, (float)(b * kLog2e), (float)(b * kInvPi));
+  // past the end: the last point with weight 0 (a point of no width anywhere else
+  // would be 0 times infinity at a cell whose distance from it overflows)
+  auto fetch = [&](int64_t j) {
+    const int64_t i = j < n ? j : n - 1;
+    const float2 p = y[i];
+    const double b = beta[i];
+    return make_float4(p.x, p.y, (float)(b * kLog2e), j < n ? (float)(b * kInvPi) : 0.f);
   };
   float4 next = c0 < c1 ? fetch(c0 * kKdeChunk + l) : make_float4(0.f, 0.f, 0.f, 0.f);
   for (int64_t c = c0; c < c1; ++c) {
