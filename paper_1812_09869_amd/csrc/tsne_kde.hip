@@ -50,9 +50,10 @@ __global__ __launch_bounds__(64 * kKdeWaves) void k_kde_raster(const float2 *__r
                                                                float *__restrict__ out) {
   __shared__ KdeSmem sm;
   const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 31, lk = l >> 5;
-  const unsigned across = (unsigned)((g.gx + kKdeTile - 1) / kKdeTile);
-  const int64_t u0 = (int64_t)(blockIdx.x % across) * kKdeTile,
-                v0 = (int64_t)(blockIdx.x / across) * kKdeTile;
+  const unsigned across = (unsigned)(((int64_t)g.gx + kKdeTile - 1) / kKdeTile);
+  const unsigned tile = blockIdx.y * gridDim.x + blockIdx.x;
+  const int64_t u0 = (int64_t)(tile % across) * kKdeTile, v0 = (int64_t)(tile / across) * kKdeTile;
+  if (v0 >= g.gy) return;  // past the last tile (the grid's last row)
   const float cx = g.x0 + ((float)(u0 + li) + 0.5f) * g.cx;
   const float cy = g.y0 + ((float)(v0 + li) + 0.5f) * g.cy;
   // this wave's points: whole chunks
@@ -113,7 +114,13 @@ hipError_t launch_kde_raster(const float *y, int64_t n, const double *beta, cons
   static_assert(sizeof(KdeSmem) <= 160 * 1024, "one workgroup per compute unit");
   const int64_t tiles = (((int64_t)g.gx + kKdeTile - 1) / kKdeTile) *
                         (((int64_t)g.gy + kKdeTile - 1) / kKdeTile);
-  hipLaunchKernelGGL(k_kde_raster, dim3((unsigned)tiles), dim3(64 * kKdeWaves), 0, st,
+  // tiles over both grid dimensions: a launch holds fewer than 2^32 threads along x, and a raster
+  // of one row or column of 2^30 cells has 2^25 tiles
+  constexpr int64_t kAlong = (int64_t)1 << 20;
+  static_assert(kAlong * 64 * kKdeWaves < ((int64_t)1 << 32), "threads along x");
+  const dim3 grid((unsigned)(tiles < kAlong ? tiles : kAlong),
+                  (unsigned)((tiles + kAlong - 1) / kAlong));
+  hipLaunchKernelGGL(k_kde_raster, grid, dim3(64 * kKdeWaves), 0, st,
                      reinterpret_cast<const float2 *>(y), beta, n, g, out);
   return hipGetLastError();
 }
