@@ -844,11 +844,11 @@ __global__ __launch_bounds__(kCalThreads) void k_calibrate(const float *__restri
     const int I = (int)(i / T);
 #pragma unroll
     for (int q = 0; q < VPT; ++q) {
+      if (!__builtin_amdgcn_ballot_w64(!(v[q] >= far))) continue;
       // groups past the last tile have none, whatever far came to (a row whose search ends
       // without a finite sum has no limit: all of its tiles are marked)
       const int J = (q * kCalThreads + wv * 64) / T;
-      if (J >= nb || !__builtin_amdgcn_ballot_w64(!(v[q] >= far))) continue;
-      if (ln == 0) cand[tile_start(min(I, J), nb) + (I < J ? J - I : I - J)] = 1;
+      if (ln == 0 && J < nb) cand[tile_start(min(I, J), nb) + (I < J ? J - I : I - J)] = 1;
     }
   }
   if (tid == 0) {
