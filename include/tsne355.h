@@ -134,7 +134,10 @@ typedef struct {
  * mode; 0 if the arguments are out of range. Host-only, no device work.
  * (The distance mode is the only option the size depends on, so it is
  * passed alone rather than as a tsne_aff_opts; an implicit-P workspace has
- * its own size function below.) */
+ * its own size function below.) From 1,025 to 4,096 points the affinity stage
+ * is faster in a workspace with room for the n x n FP32 distances behind these
+ * bytes, 4 m^2 more with m = n rounded up to a multiple of 256; the results are
+ * the same. */
 TSNE_API size_t tsne_workspace_bytes(int64_t n, int32_t d, int32_t dist_mode);
 
 /*

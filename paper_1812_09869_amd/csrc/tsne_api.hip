@@ -42,11 +42,12 @@ Layout make_layout(int64_t n, int32_t d, int32_t mode, bool stats_only, bool imp
   L.r = take(np * 4);
   L.evals = take(np * 4);
   L.split = L.nb <= kSplitNb ? kUnits : 1;
-  L.part = take(sz * (size_t)L.nb * L.nb * L.split * T * 16);
-  L.zpart = take(sz * (size_t)L.nt * 4 * kUnits);
+  const size_t part_bytes = sz * (size_t)L.nb * L.nb * L.split * T * 16;
+  if (L.split == 1) L.part = take(part_bytes);
+  L.zpart = take(sz * (size_t)L.nt * (L.split > 1 ? 4 * kUnits : 8));
   L.cpart = take(sz * (size_t)L.nt * 16);
   L.ppart = take(sz * (size_t)L.nt * 16);
-  L.meanpart = take(sz * (size_t)L.nb * kMeanPartsPerBlock * 16);
+  L.meanpart = take(sz * (size_t)L.nb * (L.split > 1 ? kMeanPartsPerBlock : 2) * 16);
   L.nz = take(sz * (size_t)L.nt);
   L.tmap = take(sz * (size_t)L.nt * 8);
   L.tlist = take(sz * (size_t)L.nt * 4);
@@ -66,13 +67,19 @@ Layout make_layout(int64_t n, int32_t d, int32_t mode, bool stats_only, bool imp
     const int64_t tiles = implicit ? (cap < L.nt ? cap : L.nt) : L.nt;
     L.P = take(sz * (size_t)tiles * T * T * 4);
   }
-  L.iter_end = o;
-  // affinity-stage scratch (only needed inside tsne_affinities)
+  // affinity-stage scratch (only needed inside tsne_affinities). The distance
+  // block comes first, where its place does not depend on d or the mode: the
+  // iteration of a problem in units keeps its partial sums there (the affinity
+  // stage has ended by then), which are four times those of whole tiles.
+  L.cal_group = L.nb < kCalGroup ? L.nb : kCalGroup;
+  const size_t dblock_bytes = (size_t)L.cal_group * T * np * 4;
+  L.dblock = take(dblock_bytes);
+  static_assert(kSplitNb * kUnits * 16 <= kCalGroup * T * 4 && kUnits * 16 <= T * 4,
+                "the partial sums of a problem in units fit in its distance block");
+  if (L.split > 1) L.part = L.dblock;
   L.xmean = take((size_t)L.dpad * 8);
   L.xcT = take((size_t)L.dpad * np * 8);
   L.norms = take(np * 8);
-  L.cal_group = (L.nb <= kCalWhole && !stats_only) || L.nb < kCalGroup ? L.nb : kCalGroup;
-  L.dblock = take((size_t)L.cal_group * T * np * 4);
   L.npow2 = 1;
   while (L.npow2 < n) L.npow2 <<= 1;
   L.xcT2 = take(sz * (size_t)L.dpad * np * 8);
@@ -93,6 +100,17 @@ Layout make_layout(int64_t n, int32_t d, int32_t mode, bool stats_only, bool imp
   }
   L.total = o;
   return L;
+}
+
+// Room for the distances of all rows behind the layout, where the workspace has
+// it: the affinity stage then takes every row of a problem of up to kCalWhole row
+// blocks in one group.
+static void whole_group(Layout &L, size_t ws_bytes) {
+  if (L.nb <= kCalGroup || L.nb > kCalWhole) return;
+  const size_t need = (size_t)L.npad * L.npad * 4;
+  if (ws_bytes < L.total || ws_bytes - L.total < need) return;
+  L.dblock = L.total;
+  L.cal_group = L.nb;
 }
 
 }  // namespace tsne
@@ -147,10 +165,11 @@ int tsne_affinities(const float *x, int64_t n, int32_t d, double perplexity,
     return fail(TSNE_E_PERPLEXITY, "tsne_affinities: perplexity %g not in (1, n-1 = %lld)",
                 perplexity, (long long)(n - 1));
   if (!aligned(ws, 256)) return fail(TSNE_E_WORKSPACE, "tsne_affinities: ws not 256-byte aligned");
-  const Layout L = tsne::make_layout(n, d, o.dist_mode, false, o.implicit_p != 0);
+  Layout L = tsne::make_layout(n, d, o.dist_mode, false, o.implicit_p != 0);
   if (ws_bytes < L.total)
     return fail(TSNE_E_WORKSPACE, "tsne_affinities: workspace %zu bytes, need %zu", ws_bytes,
                 L.total);
+  tsne::whole_group(L, ws_bytes);
   return hip_check(tsne::launch_affinities(L, x, nullptr, perplexity, o.max_bisect, o.tol_h,
                                            o.reorder != 0, ws, (hipStream_t)stream, false,
                                            o.implicit_p != 0),
@@ -172,10 +191,11 @@ int tsne_affinities_dissim(const float *dis, int64_t n, double perplexity,
                 perplexity, (long long)(n - 1));
   if (!aligned(ws, 256))
     return fail(TSNE_E_WORKSPACE, "tsne_affinities_dissim: ws not 256-byte aligned");
-  const Layout L = tsne::make_layout(n, 1, TSNE_DIST_FP64);
+  Layout L = tsne::make_layout(n, 1, TSNE_DIST_FP64);
   if (ws_bytes < L.total)
     return fail(TSNE_E_WORKSPACE, "tsne_affinities_dissim: workspace %zu bytes, need %zu",
                 ws_bytes, L.total);
+  tsne::whole_group(L, ws_bytes);
   return hip_check(tsne::launch_affinities(L, nullptr, dis, perplexity, o.max_bisect, o.tol_h, 0,
                                            ws, (hipStream_t)stream),
                    "tsne_affinities_dissim");

@@ -28,7 +28,11 @@ constexpr int T = 256;             // tile edge
 constexpr int TT4 = T * T / 4;     // float4 per tile
 constexpr int kThreads = 256;      // threads per tile workgroup
 constexpr int kCalGroup = 4;       // row blocks per launch of the per-row search
-constexpr int kCalWhole = 16;      // up to so many (4,096 points), all of them in one launch
+// Up to so many row blocks (4,096 points) all of them in one launch, in a workspace that has room
+// for it behind its layout: distances, search and staging of 2,000 points in one group of eight
+// blocks instead of two of four 214 us against 224 (the whole affinity stage; dissimilarities 72
+// and 95), of 4,096 points 403 against 442 (132, 179).
+constexpr int kCalWhole = 16;
 // Problems of at most kSplitNb row blocks (2,048 points) run the force pass in
 // units of a quarter tile (kUnits = 4 per tile, 64 rows x 256 columns each): a
 // whole tile is 256 pairs per thread, and a small problem has too few tiles to
@@ -80,7 +84,6 @@ struct Layout {
   size_t inv = 0;   // int32 [npad]: caller's index -> internal position
   size_t yp = 0;    // float2 [npad]: the map in the internal order (per force pass)
   size_t extent = 0;  // float4 [nb]: per-block {min x, max x, min y, max y} of that map
-  size_t iter_end = 0;  // end of the part that tsne_step needs
   int32_t kk = 0;  // 16-bit operand values per point (d rounded up to 32; four slices in the x3 modes)
   int32_t cal_group = 1;  // row blocks per search launch (their distance blocks side by side)
   size_t xmean = 0, xcT = 0, norms = 0, dblock = 0;

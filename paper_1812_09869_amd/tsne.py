@@ -139,7 +139,10 @@ class BatchedTSNE:
     """
 
     def __init__(self, problems, dist_mode="fp64"):
-        self.models = [ExactTSNE(x, perp, dist_mode=dist_mode) for x, perp in problems]
+        # (many workspaces at once: the least memory)
+        self.models = [ExactTSNE(x, perp, dist_mode=dist_mode,
+                                 ws=_lib.new_workspace(*x.shape, dist_mode, device=x.device,
+                                                       room=False)) for x, perp in problems]
         self.states = None
         self._arr = None
         self._bws = None
