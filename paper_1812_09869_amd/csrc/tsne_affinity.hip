@@ -2460,10 +2460,12 @@ hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, 
 #undef TSNE_CAL
       return;
     }
+    // (below 8 points a thread only maps come here: kCalWaveN)
     auto run = [&](auto vpt) {
       constexpr int V = decltype(vpt)::value;
-      auto *k = &k_calibrate<V, kCalPlain>;
-      if constexpr (V > 0) {
+      static_assert(4 * kCalThreads <= kCalWaveN, "rows of points are searched by waves");
+      auto *k = &k_calibrate<V, (V == 0 || V > 4) ? kCalPlain : kCalMap>;
+      if constexpr (V > 4) {
         if (ordered) k = &k_calibrate<V, kCalOrdered>;
         if (map) k = &k_calibrate<V, kCalMap>;
       }
