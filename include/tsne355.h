@@ -440,8 +440,8 @@ TSNE_API int64_t tsne_mlp_param_count(int32_t d_in, int32_t hidden);
 TSNE_API size_t tsne_mlp_workspace_bytes(int32_t d_in, int32_t hidden, int64_t batch,
                                          int32_t train);
 
-/* out (n x 2 FP32) = network(x) for the n rows of x (n x d_in FP32). Rows are
- * processed in chunks of the batch size the workspace was sized for. */
+/* out (n x 2 FP32) = network(x) for the n rows of x (n x d_in FP32), in one
+ * pass whatever batch the workspace was sized for. */
 TSNE_API int tsne_mlp_forward(const float *params, int32_t d_in, int32_t hidden,
                               const float *mean, const float *invstd, const float *x, int64_t n,
                               float *out, void *ws, size_t ws_bytes, void *stream);

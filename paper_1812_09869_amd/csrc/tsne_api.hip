@@ -543,23 +543,6 @@ size_t tsne_mlp_workspace_bytes(int32_t d_in, int32_t hidden, int64_t batch, int
   return tsne::make_mlp_layout(d_in, hidden, (batch + 63) / 64 * 64, train != 0).total;
 }
 
-// Largest batch (multiple of 64) whose layout fits in ws_bytes, or 0.
-static int64_t mlp_capacity(int32_t d_in, int32_t hidden, size_t ws_bytes, bool train) {
-  if (tsne::make_mlp_layout(d_in, hidden, 64, train).total > ws_bytes) return 0;
-  int64_t lo = 64, hi = 128;
-  while (hi <= ((int64_t)1 << 28) && tsne::make_mlp_layout(d_in, hidden, hi, train).total <= ws_bytes)
-    hi *= 2;
-  while (hi - lo > 64) {
-    int64_t mid = (lo + hi) / 2 / 64 * 64;
-    if (mid <= lo) break;
-    if (tsne::make_mlp_layout(d_in, hidden, mid, train).total <= ws_bytes)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
 int tsne_mlp_forward(const float *params, int32_t d_in, int32_t hidden, const float *mean,
                      const float *invstd, const float *x, int64_t n, float *out, void *ws,
                      size_t ws_bytes, void *stream) {
@@ -569,9 +552,9 @@ int tsne_mlp_forward(const float *params, int32_t d_in, int32_t hidden, const fl
     return fail(TSNE_E_ARG, "tsne_mlp_forward: unsupported d_in %d / hidden %d / n %lld", d_in,
                 hidden, (long long)n);
   if (!aligned(ws, 256)) return fail(TSNE_E_WORKSPACE, "tsne_mlp_forward: ws not 256-byte aligned");
-  const int64_t cap = mlp_capacity(d_in, hidden, ws_bytes, false);
-  if (cap == 0) return fail(TSNE_E_WORKSPACE, "tsne_mlp_forward: workspace too small");
-  const tsne::MlpLayout L = tsne::make_mlp_layout(d_in, hidden, cap, false);
+  // (a forward pass keeps the weight copies alone, whatever the batch)
+  const tsne::MlpLayout L = tsne::make_mlp_layout(d_in, hidden, 64, false);
+  if (ws_bytes < L.total) return fail(TSNE_E_WORKSPACE, "tsne_mlp_forward: workspace too small");
   return hip_check(tsne::launch_mlp_forward(L, params, mean, invstd, x, n, out, ws,
                                             (hipStream_t)stream),
                    "tsne_mlp_forward");
