@@ -911,7 +911,11 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
   // zero and its curvature -Var(d), so it falls to ln u near
   // beta = sqrt(2 ln((n - 1) / u) / Var(d)); one pass without exponentials. (From
   // beta = 1, partial problems of 1,000 points at perplexity 400 took 13 passes,
-  // most of them halvings; from here 4.)
+  // most of them halvings; from here 4.) Where far points make up the variance
+  // (clusters a thousand widths apart, one stray point), the start is far too
+  // small and the first Newton step, over the near points' variance, far too
+  // large; a bracket so wide is halved in the exponent (1,000 points, two clusters:
+  // 19 passes by halves, 9 so).
   double beta, lo = 0.0, hi = INFINITY;
   {
     double T1[R], T2[R];
@@ -985,8 +989,10 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
       const double nb = beta + (f.H - logu) / (beff * var);
       if (var > 0.0 && nb > lo && nb < hi && isfinite(nb))
         beta = nb;
+      else if (isinf(hi))
+        beta = 2.0 * beta;
       else
-        beta = isinf(hi) ? 2.0 * beta : 0.5 * (lo + hi);
+        beta = lo > 0.0 && hi > 16.0 * lo ? sqrt(lo) * sqrt(hi) : 0.5 * (lo + hi);
     }
   }
   return f;
