@@ -423,8 +423,7 @@ int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *bat
   bh->magic = tsne::kBatchMagic;
   bh->count = count;
   bh->total_tiles = tot.tiles;
-  bh->total_blocks = tot.blocks;
-  bh->total_units = tot.units;
+  bh->total_rest = tot.rest();
   tsne::BatchEntry *tab = reinterpret_cast<tsne::BatchEntry *>(host + tsne::kBatchHdrBytes);
   int64_t t0 = 0, u0 = 0;
   int32_t b0 = 0;

@@ -172,12 +172,14 @@ struct BatchHdr {
   uint64_t magic;
   int32_t count;
   int32_t pad;
-  int64_t total_tiles, total_blocks, total_units;
+  int64_t total_tiles, total_rest;
 };
 // Totals of a batch, computed on the host from the problems' sizes. units:
 // quarter tiles of the problems that are split; whole: tiles of the others.
 struct BatchTotals {
   int64_t tiles = 0, blocks = 0, units = 0, whole = 0;
+  // blocks and units (each below 2^31) in one word of the plan's check
+  int64_t rest() const { return blocks | units << 32; }
 };
 constexpr size_t kBatchHdrBytes = 256;
 

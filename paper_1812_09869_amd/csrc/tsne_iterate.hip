@@ -1402,10 +1402,12 @@ __device__ inline int find_entry(const BatchEntry *tab, int count, int64_t key, 
 }
 
 // The launch must match the plan held in the batch workspace. Every kernel of a
-// step asks for all of it, so that none runs where another has not.
-__device__ inline bool batch_ok(const BatchHdr *bh, int count, const BatchTotals &tot) {
-  return bh->magic == kBatchMagic && bh->count == count && bh->total_tiles == tot.tiles &&
-         bh->total_blocks == tot.blocks && bh->total_units == tot.units;
+// step asks for all of it, so that none runs where another has not. rest: row
+// blocks and units in one word (a fourth argument of their own cost the
+// persistent kernel 2%).
+__device__ inline bool batch_ok(const BatchHdr *bh, int count, int64_t tiles, int64_t rest) {
+  return bh->magic == kBatchMagic && bh->count == count && bh->total_tiles == tiles &&
+         bh->total_rest == rest;
 }
 
 __device__ inline const BatchEntry *batch_table(const BatchHdr *bh) {
@@ -1436,10 +1438,10 @@ __device__ inline int find_unit_entry(const BatchEntry *tab, int count, int64_t 
 
 // Units of the split problems, `per` (1, 2 or 4) of one tile to a workgroup.
 __global__ __launch_bounds__(256, 2) void k_force_unit_batched(const BatchHdr *__restrict__ bh,
-                                                               int count, BatchTotals tot,
-                                                               int per) {
+                                                               int count, int64_t tiles,
+                                                               int64_t rest, int per) {
   __shared__ UnitSmem sm;
-  if (!batch_ok(bh, count, tot)) return;
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int64_t key = (int64_t)blockIdx.x * per;
   const BatchEntry &e = tab[__builtin_amdgcn_readfirstlane(find_unit_entry(tab, count, key))];
@@ -1469,9 +1471,10 @@ union BatchSmem {
 // position within its problem is past the count of all-zero tiles exits at
 // once.
 __global__ __launch_bounds__(256, 4) void k_force_zero_batched(const BatchHdr *__restrict__ bh,
-                                                               int count, BatchTotals tot) {
+                                                               int count, int64_t tiles,
+                                                               int64_t rest) {
   __shared__ BatchSmem<ZeroSmem> sm;
-  if (!batch_ok(bh, count, tot)) return;
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int p = find_entry(tab, count, blockIdx.x, true);
   const BatchEntry &e = tab[p];
@@ -1497,13 +1500,14 @@ __global__ __launch_bounds__(256, 4) void k_force_zero_batched(const BatchHdr *_
 // units in turn) to a workgroup, for batches of at most kAnyTilesBatched tiles
 // (k_force_any says why).
 __global__ __launch_bounds__(256, 2) void k_force_any_batched(const BatchHdr *__restrict__ bh,
-                                                              int count, BatchTotals tot) {
+                                                              int count, int64_t tiles,
+                                                              int64_t rest) {
   __shared__ union {
     ForceSmem full;
     ZeroSmem zero;
     UnitSmem unit;
   } sm;
-  if (!batch_ok(bh, count, tot)) return;
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int p = find_entry(tab, count, blockIdx.x, true);
   const BatchEntry &e = tab[p];
@@ -1564,11 +1568,12 @@ constexpr int kBatchLds = 1024;
 // both loops in one kernel the tile bodies spill).
 template <bool WALK>
 __global__ __launch_bounds__(256, 2) void k_force_full_batched(const BatchHdr *__restrict__ bh,
-                                                               int count, BatchTotals tot) {
+                                                               int count, int64_t tiles,
+                                                               int64_t rest) {
   __shared__ BatchSmem<ForceSmem> sm;
   __shared__ int64_t pre[WALK ? 1 : kBatchLds + 1];  // list position of a problem's first nonzero tile
   __shared__ int64_t nzero_s;
-  if (!batch_ok(bh, count, tot)) return;
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int t = threadIdx.x;
   if constexpr (!WALK) {
@@ -1666,8 +1671,8 @@ __global__ __launch_bounds__(256, 2) void k_force_full_batched(const BatchHdr *_
 }
 
 __global__ __launch_bounds__(256) void k_gather_batched(const BatchHdr *__restrict__ bh,
-                                                        int count, BatchTotals tot) {
-  if (!batch_ok(bh, count, tot)) return;
+                                                        int count, int64_t tiles, int64_t rest) {
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int p = find_entry(tab, count, blockIdx.x, false);
   const BatchEntry &e = tab[p];
@@ -1678,11 +1683,12 @@ __global__ __launch_bounds__(256) void k_gather_batched(const BatchHdr *__restri
 }
 
 __global__ __launch_bounds__(kUpd, 8) void k_update_batched(const BatchHdr *__restrict__ bh,
-                                                            int count, BatchTotals tot,
+                                                            int count, int64_t tiles,
+                                                            int64_t rest,
                                                             float alpha, float mu, float eta,
                                                             float min_gain, int lr_rule) {
   __shared__ UpdSmem sm;
-  if (!batch_ok(bh, count, tot)) return;
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int64_t gb = (int64_t)blockIdx.x / kUpdPerBlock;  // global row block
   const int p = find_entry(tab, count, gb, false);
@@ -1699,9 +1705,10 @@ __global__ __launch_bounds__(kUpd, 8) void k_update_batched(const BatchHdr *__re
 }
 
 __global__ __launch_bounds__(256) void k_recentre_batched(const BatchHdr *__restrict__ bh,
-                                                          int count, BatchTotals tot) {
+                                                          int count, int64_t tiles,
+                                                          int64_t rest) {
   __shared__ float2 smean;
-  if (!batch_ok(bh, count, tot)) return;
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int p = find_entry(tab, count, blockIdx.x, false);
   const BatchEntry &e = tab[p];
@@ -1890,8 +1897,9 @@ __global__ __launch_bounds__(1024) void k_cost_reduce(const double2 *__restrict_
 // Cost of every problem of a batch: one workgroup per tile, then one per
 // problem (out: device double[2 count], {KL, C_norm} per problem).
 __global__ __launch_bounds__(256, 2) void k_cost_batched(const BatchHdr *__restrict__ bh,
-                                                         int count, BatchTotals tot) {
-  if (!batch_ok(bh, count, tot)) return;
+                                                         int count, int64_t tiles,
+                                                         int64_t rest) {
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
   const int p = find_entry(tab, count, blockIdx.x, true);
   const BatchEntry &e = tab[p];
@@ -1901,9 +1909,9 @@ __global__ __launch_bounds__(256, 2) void k_cost_batched(const BatchHdr *__restr
 }
 
 __global__ __launch_bounds__(1024) void k_cost_reduce_batched(const BatchHdr *__restrict__ bh,
-                                                              int count, BatchTotals tot,
-                                                              double *out) {
-  if (!batch_ok(bh, count, tot)) return;
+                                                              int count, int64_t tiles,
+                                                              int64_t rest, double *out) {
+  if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry &e = batch_table(bh)[blockIdx.x];
   cost_reduce_wg(e.cpart, e.nt, e.n, e.h, out + 2 * (int64_t)blockIdx.x);
 }
@@ -2125,10 +2133,11 @@ hipError_t launch_batch_cost(const void *batch_ws, int count, const BatchTotals 
                              hipStream_t st) {
   const BatchHdr *bh = reinterpret_cast<const BatchHdr *>(batch_ws);
   hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
-                     tot);
-  hipLaunchKernelGGL(k_cost_batched, dim3((unsigned)tot.tiles), dim3(256), 0, st, bh, count, tot);
+                     tot.tiles, tot.rest());
+  hipLaunchKernelGGL(k_cost_batched, dim3((unsigned)tot.tiles), dim3(256), 0, st, bh, count,
+                     tot.tiles, tot.rest());
   hipLaunchKernelGGL(k_cost_reduce_batched, dim3((unsigned)count), dim3(1024), 0, st, bh, count,
-                     tot, out);
+                     tot.tiles, tot.rest(), out);
   return hipGetLastError();
 }
 
@@ -2144,14 +2153,14 @@ hipError_t launch_batch_step(const void *batch_ws, int count, const BatchTotals 
     // 4: 66 us)
     const int per = tot.units >= 4 * kFullGrid ? 4 : tot.units >= 2 * kFullGrid ? 2 : 1;
     hipLaunchKernelGGL(k_force_unit_batched, dim3((unsigned)(tot.units / per)), dim3(256), 0, st,
-                       bh, count, tot, per);
+                       bh, count, tot.tiles, tot.rest(), per);
   } else {
     hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
-                       tot);
+                       tot.tiles, tot.rest());
   }
   if (tot.whole > 0 && tot.tiles <= kAnyTilesBatched) {
     hipLaunchKernelGGL(k_force_any_batched, dim3((unsigned)tot.tiles), dim3(256), 0, st, bh, count,
-                       tot);
+                       tot.tiles, tot.rest());
   } else if (tot.whole > 0) {
     std::lock_guard<std::mutex> lock(g_side_mu);
     SideStream *ss = nullptr;
@@ -2161,23 +2170,23 @@ hipError_t launch_batch_step(const void *batch_ws, int count, const BatchTotals 
     const unsigned full_grid = (unsigned)(tot.tiles < kFullGrid ? tot.tiles : kFullGrid);
     if (count <= kBatchLds)
       hipLaunchKernelGGL(k_force_full_batched<false>, dim3(full_grid), dim3(256), 0, st, bh, count,
-                         tot);
+                         tot.tiles, tot.rest());
     else
       hipLaunchKernelGGL(k_force_full_batched<true>, dim3(full_grid), dim3(256), 0, st, bh, count,
-                         tot);
+                         tot.tiles, tot.rest());
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(ss->s, ss->fork, 0)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_force_zero_batched, dim3((unsigned)tot.tiles), dim3(256), 0, ss->s, bh,
-                       count, tot);
+                       count, tot.tiles, tot.rest());
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipEventRecord(ss->join, ss->s)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(st, ss->join, 0)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_update_batched, dim3((unsigned)(tot.blocks * kUpdPerBlock)), dim3(kUpd), 0,
-                     st, bh, count, tot, alpha, mu, eta, min_gain, lr_rule);
+                     st, bh, count, tot.tiles, tot.rest(), alpha, mu, eta, min_gain, lr_rule);
   if (recentre)
     hipLaunchKernelGGL(k_recentre_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
-                       tot);
+                       tot.tiles, tot.rest());
   return hipGetLastError();
 }
 
