@@ -425,7 +425,7 @@ int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *bat
   bh->total_tiles = tot.tiles;
   bh->total_rest = tot.rest();
   tsne::BatchEntry *tab = reinterpret_cast<tsne::BatchEntry *>(host + tsne::kBatchHdrBytes);
-  int64_t t0 = 0, u0 = 0;
+  int64_t t0 = 0;
   int32_t b0 = 0;
   for (int32_t p = 0; p < count; ++p) {
     const tsne::Layout L = tsne::make_layout(problems[p].n, 1, TSNE_DIST_FP64);
@@ -455,8 +455,6 @@ int tsne_batch_plan(const tsne_batch_problem *problems, int32_t count, void *bat
     e.tile0 = t0;
     e.blk0 = b0;
     e.split = L.split;
-    e.unit0 = u0;
-    if (L.split > 1) u0 += L.nt * L.split;
     t0 += L.nt;
     b0 += L.nb;
   }

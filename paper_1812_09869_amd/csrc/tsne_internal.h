@@ -134,7 +134,6 @@ struct BatchEntry {
   Hdr *h;
   int64_t n, nt, tile0;  // tile0: first global tile index of this problem
   int32_t nb, blk0;      // blk0: first global row-block index of this problem
-  int64_t unit0;         // first global unit (problems with split = kUnits; the others have none)
   int32_t split, pad;
 };
 

@@ -573,9 +573,15 @@ __global__ __launch_bounds__(256, 2) void k_force_full(const float4 *__restrict_
 // 140, 65,536 807 against 708.
 constexpr int64_t kAnyTiles = 2850;
 // For a batch, by all its tiles: 501 tiles 46 us a sweep against 70, 1,341 78
-// against 102, 2,146 95 against 114, 5,796 225 against 227, 21,753 676 against
-// 611.
-constexpr int64_t kAnyTilesBatched = 4096;
+// against 102, 2,146 95 against 114, 4,986 (problems of 2,000 to 6,000 points) 209
+// against 216, 6,393 258 against 260, 21,753 676 against 611. And for batches at
+// least half of whose tiles are small problems': units in turn take the two
+// kernels' time and a tenth more, and one launch makes up for it (400 problems of
+// 1,000 to 2,500 points, 12,563 tiles, 82% with P: 738 us against 793, 51%: 605
+// against 658; of 1,000 to 2,048, 9,706 tiles: 628 against 671, 510 against 555).
+// Below half it depends on P (200 of 1,000 to 4,000, 13% small problems' tiles:
+// 594 against 642 with P in 64% of the tiles, 495 against 465 in 36%).
+constexpr int64_t kAnyTilesBatched = 6000;
 __global__ __launch_bounds__(256, 2) void k_force_any(const float4 *__restrict__ P,
                                                       const float2 *__restrict__ Y, int64_t n,
                                                       int32_t nb, float4 *__restrict__ part,
@@ -1415,44 +1421,41 @@ __device__ inline const BatchEntry *batch_table(const BatchHdr *bh) {
                                               kBatchHdrBytes);
 }
 
-// Last entry whose first unit is not after `key`, entry 0's being 0. The wave looks
-// at 128 entries at a time (two loads a lane, in flight together) and goes on
-// between two of them: one memory latency up to 128 problems, two up to 16,384,
-// three beyond, where halving takes seven for 128. Problems that are not split
-// have no units: they share their successor's first unit and are never the last;
-// a run of them at the end of the table starts past every unit.
-__device__ inline int find_unit_entry(const BatchEntry *tab, int count, int64_t key) {
+// The entry that holds tile `key`. The wave looks at 128 entries at a time (two
+// loads a lane, in flight together) and goes on between two of them: one memory
+// latency up to 128 problems, two up to 16,384, three beyond, where halving takes
+// seven for 128. For the kernels whose workgroups do little else.
+__device__ inline int find_tile_entry(const BatchEntry *tab, int count, int64_t key) {
   const int l = threadIdx.x & 63;
   int lo = 0, len = count;
   while (len > 1) {
     const int step = (len + 127) / 128;
     const int64_t p0 = (int64_t)l * step, p1 = (int64_t)(l + 64) * step;
-    const bool below0 = p0 < len && tab[lo + p0].unit0 <= key;
-    const bool below1 = p1 < len && tab[lo + p1].unit0 <= key;
+    const bool below0 = p0 < len && tab[lo + p0].tile0 <= key;
+    const bool below1 = p1 < len && tab[lo + p1].tile0 <= key;
     const int at = (__popcll(__ballot(below0)) + __popcll(__ballot(below1)) - 1) * step;
     lo += at;
     len = min(step, len - at);
   }
-  return lo;
+  return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// Units of the split problems, `per` (1, 2 or 4) of one tile to a workgroup.
+// Units of the split problems, `per` (1 or 2) of one tile to a workgroup.
 __global__ __launch_bounds__(256, 2) void k_force_unit_batched(const BatchHdr *__restrict__ bh,
                                                                int count, int64_t tiles,
                                                                int64_t rest, int per) {
   __shared__ UnitSmem sm;
   if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
-  const int64_t key = (int64_t)blockIdx.x * per;
-  const BatchEntry &e = tab[__builtin_amdgcn_readfirstlane(find_unit_entry(tab, count, key))];
-  const int64_t u = key - e.unit0;
-  if (e.split != kUnits || u < 0 || u >= e.nt * kUnits) return;
+  const unsigned unit = blockIdx.x * (unsigned)per;
+  const BatchEntry &e = tab[find_tile_entry(tab, count, unit / kUnits)];
+  const int64_t tile = (int64_t)(unit / kUnits) - e.tile0;
+  const int p = (int)(unit % kUnits);
+  if (e.split != kUnits || tile < 0 || tile >= e.nt) return;
   if (!ready_is(e.h, e.n, 1)) {
-    if (u == 0 && threadIdx.x == 0) flag_error(e.h, kErrState);
+    if (tile == 0 && p == 0 && threadIdx.x == 0) flag_error(e.h, kErrState);
     return;
   }
-  const int64_t tile = u / kUnits;
-  const int p = (int)(u % kUnits);
   unit_body<0>(e.P, e.Y, e.perm, e.n, e.nb, e.part, e.zpart, e.extent, e.tmap[tile],
             e.nz[tile] != 0, tile, tile, p, p + per, sm);
 }
@@ -1497,8 +1500,8 @@ __global__ __launch_bounds__(256, 4) void k_force_zero_batched(const BatchHdr *_
 }
 
 // Every tile of the batch in one launch, a tile (of a split problem: its four
-// units in turn) to a workgroup, for batches of at most kAnyTilesBatched tiles
-// (k_force_any says why).
+// units in turn) to a workgroup. kAnyTilesBatched says for which batches,
+// k_force_any why.
 __global__ __launch_bounds__(256, 2) void k_force_any_batched(const BatchHdr *__restrict__ bh,
                                                               int count, int64_t tiles,
                                                               int64_t rest) {
@@ -1509,7 +1512,7 @@ __global__ __launch_bounds__(256, 2) void k_force_any_batched(const BatchHdr *__
   } sm;
   if (!batch_ok(bh, count, tiles, rest)) return;
   const BatchEntry *tab = batch_table(bh);
-  const int p = find_entry(tab, count, blockIdx.x, true);
+  const int p = find_tile_entry(tab, count, blockIdx.x);
   const BatchEntry &e = tab[p];
   const int64_t tile = (int64_t)blockIdx.x - e.tile0;
   if (tile < 0 || tile >= e.nt) return;
@@ -2145,23 +2148,24 @@ hipError_t launch_batch_step(const void *batch_ws, int count, const BatchTotals 
                              float mu, float eta, float min_gain, int recentre, int lr_rule,
                              hipStream_t st) {
   const BatchHdr *bh = reinterpret_cast<const BatchHdr *>(batch_ws);
-  if (tot.whole == 0) {
-    // split problems only: no gather, one force launch, one stream. Units per
-    // workgroup: a workgroup of more units reads its columns and finds its
-    // problem once for all of them, so as many as still leave two workgroups
-    // for every compute unit (4,800 units: 1 to a workgroup 110 us, 2: 80 us,
-    // 4: 66 us)
-    const int per = tot.units >= 4 * kFullGrid ? 4 : tot.units >= 2 * kFullGrid ? 2 : 1;
+  // Split problems only, and few: no gather, one unit to a workgroup, two from two for
+  // every place on the chip. Beyond three, a tile's four units in turn read their
+  // columns, from the gathered map, and find their problem once (72 tiles 22.6 us a
+  // sweep against 33.3, 288 42 against 45, 432 49 against 47, 1,400 124 against 118,
+  // 9,706 677 against 628).
+  const bool units = tot.whole == 0 && tot.units <= 3 * kFullGrid;
+  if (units) {
+    const int per = tot.units >= 2 * kFullGrid ? 2 : 1;
     hipLaunchKernelGGL(k_force_unit_batched, dim3((unsigned)(tot.units / per)), dim3(256), 0, st,
                        bh, count, tot.tiles, tot.rest(), per);
   } else {
     hipLaunchKernelGGL(k_gather_batched, dim3((unsigned)tot.blocks), dim3(256), 0, st, bh, count,
                        tot.tiles, tot.rest());
   }
-  if (tot.whole > 0 && tot.tiles <= kAnyTilesBatched) {
+  if (!units && (tot.tiles <= kAnyTilesBatched || tot.units >= 2 * tot.tiles)) {
     hipLaunchKernelGGL(k_force_any_batched, dim3((unsigned)tot.tiles), dim3(256), 0, st, bh, count,
                        tot.tiles, tot.rest());
-  } else if (tot.whole > 0) {
+  } else if (!units) {
     std::lock_guard<std::mutex> lock(g_side_mu);
     SideStream *ss = nullptr;
     hipError_t e = side_stream(ss);

@@ -1,6 +1,7 @@
-"""Batches of more than 4,096 tiles that mix problems whose force pass runs in quarter tiles (at
-most 2,048 points) with larger ones: one persistent workgroup takes tiles of both kinds in turn, on
-the same LDS. Bitwise against separate runs."""
+"""Batches of more than 6,000 tiles that mix problems whose force pass runs in quarter tiles (at
+most 2,048 points) with larger ones, whose tiles are the most: one persistent workgroup takes tiles
+of both kinds in turn, on the same LDS. Bitwise against separate runs. And batches at the lines
+between the launches."""
 import numpy as np
 import pytest
 import torch
@@ -25,7 +26,8 @@ def _compare(ns, chosen, iters, seed):
     # one component: every tile holds P, so all of them are the persistent kernel's
     probs = [((rng.standard_normal((n, 3)) * 3).astype(np.float32), 8.0) for n in ns]
     y0s = [synth.embedding_init(n, seed=900 + k) for k, n in enumerate(ns)]
-    assert sum(_tiles(n) for n in ns) > 4096
+    assert sum(_tiles(n) for n in ns) > 6000
+    assert 2 * sum(_tiles(n) for n in ns if n <= 2048) < sum(_tiles(n) for n in ns)
     print(f"\n[mixed] {len(ns)} problems, {sum(_tiles(n) for n in ns)} tiles", flush=True)
     batched = BatchedTSNE([(_t(x), p) for x, p in probs])
     batched.init_states([_t(y) for y in y0s])
@@ -46,7 +48,7 @@ def test_small_problems_after_large_ones():
     512 workgroups' turns, in both orders. Every problem is compared."""
     rng = np.random.Generator(np.random.PCG64(51))
     ns = []
-    for _ in range(46):
+    for _ in range(62):
         ns += [int(rng.integers(2049, 4300)), int(rng.integers(1200, 2049))]
     _compare(ns, range(len(ns)), 4, 52)
 
@@ -57,8 +59,32 @@ def test_more_than_1024_problems_of_both_kinds():
     boundary are compared."""
     rng = np.random.Generator(np.random.PCG64(53))
     ns = [int(v) for v in rng.integers(40, 300, 1030)]
-    large = {0: 14000, 300: 2049, 700: 7000, 1023: 9000, 1025: 2300, 1029: 4097}
+    large = {0: 20000, 300: 2049, 700: 8000, 1023: 9000, 1025: 6000, 1029: 4097}
     for k, n in large.items():
         ns[k] = n
     chosen = sorted({min(max(k + o, 0), 1029) for k in large for o in (-1, 0, 1)} | {511})
     _compare(ns, chosen, 3, 54)
+
+
+@pytest.mark.parametrize("ns", [
+    [2000] * 7,                  # 1,008 units, one to a workgroup
+    [2000] * 8,                  # 1,152, two to a workgroup
+    [2000] * 11 + [700],         # 1,608: whole tiles' launch
+    [2040] * 150 + [20000],      # 8,560 tiles, 5,400 of them small problems': one launch
+], ids=["one", "two", "four", "most"])
+def test_lines_between_launches(ns):
+    rng = np.random.Generator(np.random.PCG64(len(ns)))
+    probs = [((rng.standard_normal((n, 3)) * 3).astype(np.float32), 8.0) for n in ns]
+    y0s = [synth.embedding_init(n, seed=70 + k) for k, n in enumerate(ns)]
+    print(f"\n[mixed] {len(ns)} problems, {sum(_tiles(n) for n in ns)} tiles", flush=True)
+    batched = BatchedTSNE([(_t(x), p) for x, p in probs])
+    batched.init_states([_t(y) for y in y0s])
+    batched.run(2, sched=Schedule(switch=1))
+    assert max(m.status() for m in batched.models) == 0
+    for k in sorted({0, 1, len(ns) // 2, len(ns) - 2, len(ns) - 1}):
+        x, p = probs[k]
+        single = ExactTSNE(_t(x), p)
+        st = single.init_state(_t(y0s[k]))
+        single.run(st, 2, sched=Schedule(switch=1))
+        for a, b in zip(batched.states[k], st):
+            assert torch.equal(a, b), (k, ns[k])
