@@ -217,7 +217,7 @@ TSNE_API int tsne_cost(void *ws, int64_t n, const float *y, double *out, void *s
  * input in FP64, or the FP32 / 16-bit operands of a reduced distance mode)
  * and a buffer of tiles. The affinity stage ends with one pass over every
  * tile that finds the all-zero tiles of P; every force pass and cost
- * evaluation then recomputes the nonzero tiles buffer by buffer (their
+ * evaluation then recomputes the nonzero tiles (their
  * distances on MFMA in the workspace's distance mode, Eq. 1 with the stored
  * beta, m and S, Eq. 3) and consumes them at once, and gives the zero tiles
  * the repulsion-only body. P, gradients, costs and maps are bitwise those of

@@ -2265,13 +2265,15 @@ __global__ __launch_bounds__(1024) void k_small_lists(const SmallEntry *__restri
 }
 
 // ----------------------------------------------------------------------------
-// 6. Implicit P: the workspace keeps a buffer of whole block rows of tiles
-// (at most 2,048 tiles, at least one block row); every pass recomputes the
-// distances of each block b of the rows in the buffer (the same MFMA kernel as
-// the affinity stage, from the centred X in the internal order) and stages
-// its tiles (b, b .. nb - 1), then packs the buffer, slot x holding tile
-// base + x. The arithmetic is that of the stored P, so the values
-// are bitwise the same.
+// 6. Implicit P: the workspace keeps a buffer of implicit_capacity(L) tiles. The
+// affinity stage ends with one pass over every tile (launch_implicit_discover):
+// by buffers of whole block rows, k_tdist forms the distances, slot x holding tile
+// base + x, and k_pack_range packs them, which gives the zero tiles, the sums of P
+// and the lists. Later passes leave the zero tiles out and form the P of the others
+// with their distances (k_tdist with PACK; above kImplicitTiles tiles a force pass
+// takes a tile at a time, in a slot of the buffer for each workgroup:
+// k_force_implicit). The arithmetic is that of the stored P, so the values are
+// bitwise the same.
 // ----------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_pack_range(float4 *__restrict__ Pb,
                                                     const float *__restrict__ a,
@@ -2298,8 +2300,8 @@ __global__ __launch_bounds__(1024) void k_implicit_sums(const double2 *__restric
   pack_reduce_wg(ppart, nt, h, 2);
 }
 
-// End of an implicit affinity stage: no tile flagged nonzero and empty slot
-// lists until the first pass builds them, then the mode in the header.
+// Before the pass that discovers an implicit P's zero tiles: no tile flagged and
+// empty slot lists (the pass writes both).
 __global__ __launch_bounds__(256) void k_implicit_init(uint8_t *__restrict__ nz, int64_t nt,
                                                        int32_t *__restrict__ nslots, int32_t nb,
                                                        Hdr *h) {

@@ -95,8 +95,8 @@ struct Layout {
 
 // stats_only: a layout holding only what the per-row search needs (header,
 // row statistics, order, centred X and the distance block).
-// implicit: P is not stored; a buffer of whole block rows holds the P that every
-// pass recomputes (FP64 distances only).
+// implicit: P is not stored; a buffer of implicit_capacity tiles holds what a pass
+// recomputes of it.
 Layout make_layout(int64_t n, int32_t d, int32_t mode, bool stats_only = false,
                    bool implicit = false);
 
@@ -137,7 +137,6 @@ struct BatchEntry {
   int32_t split, pad;
 };
 
-// Header of a batch workspace, followed by `count` BatchEntry records.
 // Affinities of many small problems at once (n <= kSmallMaxN, d <=
 // kSmallMaxD, FP64 distances, the caller's order): one launch per phase for
 // all of them. Device table entry of one problem; wg0, tile0 and blk0 are
@@ -166,6 +165,7 @@ struct SmallEntry {
   int32_t *tlist, *tcount, *slots, *nslots, *perm, *inv;
 };
 
+// Header of a batch workspace, followed by `count` BatchEntry records.
 constexpr uint64_t kBatchMagic = 0x7453424154434801ull;
 struct BatchHdr {
   uint64_t magic;
@@ -194,9 +194,6 @@ inline P *at(void *ws, size_t off) {
 hipError_t launch_affinities(const Layout &L, const float *x, const float *dis, double perplexity,
                              int max_bisect, double tol_h, int reorder, void *ws,
                              hipStream_t stream, bool stats_only = false, bool implicit = false);
-// Implicit P: recompute block b's distances and stage its tiles into the
-// buffer; pack a range of staged tiles; after all blocks, the P sums and the
-// slot lists.
 // Implicit P: the passes check the workspace header against the shape their
 // layout was computed for, n and one word holding d (below 2^20) and the
 // distance mode (the mode decides which contraction operands exist).
@@ -209,11 +206,10 @@ inline int64_t implicit_capacity(const Layout &L) {
   const int64_t c = L.nb > kImplicitTiles ? L.nb : kImplicitTiles;
   return c < L.nt ? c : L.nt;
 }
-// Block rows [b0, b1) fill the buffer: tile t of them sits at slot
-// t - tile_start(b0). The distances of the tiles tile0 .. tile0 + count - 1,
-// written into the buffer in the staged layout, or with pack their packed
-// P (Eq. 3, the values launch_implicit_pack would leave). skip_zero: the zero
-// tiles are known (every pass after the affinity stage) and are left alone.
+// The distances of the tiles tile0 .. tile0 + count - 1, tile t at slot
+// t - tile_base of the buffer in the layout of the stored P, or with pack their
+// packed P (Eq. 3). skip_zero: the zero tiles are known (every pass after the
+// affinity stage) and are left alone.
 hipError_t launch_implicit_tiles(const Layout &L, void *ws, int64_t tile0, int64_t count,
                                  int64_t tile_base, bool skip_zero, bool pack,
                                  hipStream_t stream);
