@@ -88,3 +88,23 @@ def test_lines_between_launches(ns):
         single.run(st, 2, sched=Schedule(switch=1))
         for a, b in zip(batched.states[k], st):
             assert torch.equal(a, b), (k, ns[k])
+
+
+@pytest.mark.parametrize("n", [19201, 20001])
+def test_two_streams_against_one_launch(n):
+    """A problem of more than 2,850 tiles runs its two kinds of tile on two streams, a batch of it
+    alone in one launch: bitwise the same, with a ragged last row block and zero tiles."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    x = rng.standard_normal((n, 4)) + 40.0 * rng.standard_normal((12, 4))[rng.integers(0, 12, n)]
+    x = _t(x.astype(np.float32))
+    y0 = _t(synth.embedding_init(n, seed=n))
+    print(f"\n[mixed] n={n}, {_tiles(n)} tiles", flush=True)
+    single = ExactTSNE(x, 12.0)
+    st = single.init_state(y0)
+    single.run(st, 3, sched=Schedule(switch=2))
+    batched = BatchedTSNE([(x, 12.0)])
+    batched.init_states([y0])
+    batched.run(3, sched=Schedule(switch=2))
+    assert single.status() == 0 and batched.models[0].status() == 0
+    for a, b in zip(batched.states[0], st):
+        assert torch.equal(a, b)
