@@ -1002,8 +1002,9 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
 // many-problem path, instead of a workgroup of 1,024 threads to a row, most of
 // whose time at two points a thread went into its barriers and wave sums. All
 // rows of the problem in one launch (their distances fit in one group), each
-// from its own start. n = 2,000: 19 us against 149 (two launches). G: a workgroup to
-// a row had 1, 2 or 4 points a thread, summed in FP32, and all else in FP64; so here.
+// from its own start. n = 2,000: 22 us against 149 (two launches). G: a workgroup to
+// a row had 1, 2 or 4 points a thread, summed in FP32, and all else in FP64; so here
+// (a lane's 32 or 64 points summed in FP32: 19 us, but rows that miss tol_h).
 constexpr int64_t kCalWaveN = 4096;
 constexpr int kCalWaves = 4;  // waves per workgroup
 template <int VPT, int R, int G>
