@@ -1001,7 +1001,8 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
 // Search for problems of at most kCalWaveN points: R rows to a wave, as in the
 // many-problem path, instead of a workgroup of 1,024 threads to a row, most of
 // whose time at two points a thread went into its barriers and wave sums. All
-// rows of the problem in one launch (their distances fit in one group), each
+// rows of the problem in one launch where the workspace has room for their
+// distances (else a group of four row blocks at a time), each
 // from its own start. n = 2,000: 22 us against 149 (two launches). G: a workgroup to
 // a row had 1, 2 or 4 points a thread, summed in FP32, and all else in FP64; so here
 // (a lane's 32 or 64 points summed in FP32: 19 us, but rows that miss tol_h).
@@ -2121,7 +2122,7 @@ __global__ __launch_bounds__(256) void k_small_init(const SmallEntry *__restrict
 // row's sums and steps are those of R = 1, so its results are too. 120,000 rows
 // of 1,000 points in 30 dimensions, perplexity 400: 2.25 ms with one row to a
 // wave, 2.32 with four rows and four separate steps, 1.62 this way, 1.12 with
-// the start below. Four rows up to 1,024 points, one above, where two rows'
+// the start in search_rows. Four rows up to 1,024 points, one above, where two rows'
 // distances no longer stay in registers.
 template <int VPT, int R>
 __global__ __launch_bounds__(kSmallWaves * 64) void k_small_calibrate(
