@@ -936,16 +936,22 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
     beta = sqrt(2.0 * (log(cnt) - logu) / var);
     if (!(beta > 0.0) || !isfinite(beta)) beta = 1.0;
   }
+  // The result is that of the last pass with finite sums (of the last one if none
+  // has them): where ties at the minimum keep the entropy above its target at any
+  // beta, the search ends at the largest FP32 precision, half of the time one
+  // pass beyond it.
+  float a = 0.f;
+  bool finite = false;
   while (!__all(f.done)) {
     // a row that has stopped goes along with its last beta, unused
     if (!f.done) {
       ++f.it;
-      f.a = fmaxf((float)(beta * kLog2e), 1e-30f);
+      a = fmaxf((float)(beta * kLog2e), 1e-30f);
     }
     double SS[R], TT[R], QQ[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f.a), 16 * r));
+      const float ar = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 16 * r));
       SS[r] = TT[r] = QQ[r] = 0.0;
 #pragma unroll
       for (int q0 = 0; q0 < VPT; q0 += G) {
@@ -966,11 +972,16 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
     }
     const double ss = rows_sum_d<R>(SS), ts = rows_sum_d<R>(TT), qs = rows_sum_d<R>(QQ);
     if (f.done) continue;
-    const double beff = (double)f.a * kLn2;
-    f.S = ss;
+    const double beff = (double)a * kLn2;
     const double mean = ts / ss;
-    f.H = log(ss) + beff * mean;
-    if (fabs(f.H - logu) <= tol_h) {
+    const double H = log(ss) + beff * mean;
+    if (isfinite(H) || !finite) {
+      finite = isfinite(H);
+      f.S = ss;
+      f.H = H;
+      f.a = a;
+    }
+    if (fabs(H - logu) <= tol_h) {
       f.done = 1;
     } else if (isfinite(hi) && (hi - lo) <= hi * 0x1p-24) {
       f.done = 1;
@@ -981,12 +992,12 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
       // then take the Newton step if it lands inside it, else bisect
       // (the bracket holds the FP64 iterates; H was taken at their FP32
       // rounding beff, within 2^-24 of beta)
-      if (f.H > logu)
+      if (H > logu)
         lo = beta;
       else
         hi = beta;
       const double var = qs / ss - mean * mean;
-      const double nb = beta + (f.H - logu) / (beff * var);
+      const double nb = beta + (H - logu) / (beff * var);
       if (var > 0.0 && nb > lo && nb < hi && isfinite(nb))
         beta = nb;
       else if (isinf(hi))
