@@ -917,6 +917,7 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
   // large; a bracket so wide is halved in the exponent (1,000 points, two clusters:
   // 19 passes by halves, 9 so).
   double beta, lo = 0.0, hi = INFINITY;
+  bool spread;  // the row's distances differ
   {
     double T1[R], T2[R];
 #pragma unroll
@@ -932,6 +933,7 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
       T2[r] = (double)t2;
     }
     const double cnt = (double)(n - 1), mean = rows_sum_d<R>(T1) / cnt;
+    spread = mean > 0.0;
     const double var = rows_sum_d<R>(T2) / cnt - mean * mean;
     beta = sqrt(2.0 * (log(cnt) - logu) / var);
     if (!(beta > 0.0) || !isfinite(beta)) beta = 1.0;
@@ -939,7 +941,9 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
   // The result is that of the last pass with finite sums (of the last one if none
   // has them): where ties at the minimum keep the entropy above its target at any
   // beta, the search ends at the largest FP32 precision, half of the time one
-  // pass beyond it.
+  // pass beyond it. Where all of a row's distances are equal (identical points, a
+  // row whose input is not a number) it is that of the last pass, always beyond
+  // it: not finite, and reported.
   float a = 0.f;
   bool finite = false;
   while (!__all(f.done)) {
@@ -976,7 +980,7 @@ __device__ __forceinline__ RowSearch search_rows(float (&v)[R][VPT], int64_t n, 
     const double mean = ts / ss;
     const double H = log(ss) + beff * mean;
     if (isfinite(H) || !finite) {
-      finite = isfinite(H);
+      finite = spread && isfinite(H);
       f.S = ss;
       f.H = H;
       f.a = a;

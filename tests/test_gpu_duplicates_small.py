@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_1812_09869_amd.tsne import ExactTSNE
+from paper_1812_09869_amd.tsne import PTSNE, ExactTSNE
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +51,19 @@ def test_tied_dissimilarities(n):
     ref = np.where(k[:, None] == k[None, :], 1.0 / (n * (size[k] - 1.0))[:, None], 0.0)
     np.fill_diagonal(ref, 0.0)
     assert np.abs(P - ref).max() <= 1e-6 * ref.max()
+
+
+@pytest.mark.parametrize("n", [3, 64, 257, 700, 1025, 2048, 3000, 4096, 5000])
+def test_identical_points_are_reported(n):
+    """All distances of a row equal: no precision to be found, TSNE_E_NONFINITE at every size."""
+    print(f"\n[duplicates] identical n={n}", flush=True)
+    x = torch.ones(n, 5, device="cuda")
+    perp = min(20.0, n / 2.0)
+    model = ExactTSNE(x, perp)
+    assert model.status() == 5
+    assert not torch.isfinite(model.rowstats()[3]).any()
+    if n >= 700:  # and as partial problems
+        pt = PTSNE(x, 4, 2, perp)
+        pt.init_maps(torch.from_numpy(np.random.default_rng(n).standard_normal((n, 2))).float().cuda())
+        pt.epoch(torch.arange(n, dtype=torch.int32, device="cuda"))
+        assert pt.status() == 5
